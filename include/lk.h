@@ -287,9 +287,8 @@ enum {
   LK_OPT_TILE_A = 4,              /* FP32 LDS tile of loop A in vertices (0 = tuned) */
   LK_OPT_CHUNK_A = 5,             /* vertices of A per work item (0 = tuned) */
   LK_OPT_WAVES_PER_CU = 6,        /* persistent waves per compute unit (0 = occupancy) */
-  LK_OPT_ATAN = 7,                /* FP32 arctangent: 0 = own minimax, the R terms of a step
-                                     in phases; 1 = HIP atan2f; 2 = own minimax, term by
-                                     term (same values as 0, another instruction order) */
+  LK_OPT_ATAN = 7,                /* FP32 arctangent: 0 or 2 = own minimax (one kernel, the same
+                                     values), 1 = HIP atan2f */
   LK_OPT_SEGS_PER_LANE = 8,       /* FP32 kernel: segments of loop B per lane, 1/2/4, and 8 for
                                      CROSSINGS (0 = tuned; the direct sum uses 4 for 8) */
   LK_OPT_SEGS_PER_LANE_F64 = 9,   /* FP64 kernel: segments of loop B per lane, 1/2 (0 = tuned) */
@@ -370,7 +369,7 @@ typedef struct {
 /* Choose the kernel configuration (work split and tile shapes) for a
  * workload: times the main direct-sum kernel of this exact call (eager, HIP
  * events, on `stream`) over a coordinate-descent search of segments per lane,
- * arctangent form, small-pair batch, LDS tile, A chunk and waves per CU, applies the fastest to
+ * small-pair batch, LDS tile, A chunk and waves per CU, applies the fastest to
  * the context (as if set with lk_set_option) and returns it in *out (host).
  * cache_path (host string, may be NULL): a text file of earlier results keyed
  * by GPU architecture, mode, dtype and the workload's size profile; a hit is

@@ -315,7 +315,7 @@ hipError_t launch_bh_adapt(const BhArgs& a, int64_t n_pairs, double target, doub
 
 // --- lk_ds.hip
 // in_f64: input dtype; compute_f64: arithmetic (true = plain FP64 / refit);
-// form (FP32 only): 0 / 2 = own minimax arctangent (phased / inline), 1 = HIP
+// form (FP32 only): 0 / 2 = own minimax arctangent, 1 = HIP
 // atan2f, 3 = crossing count instead of the Eq. 4 sum; segs: segments of loop
 // B per lane (register blocking; rounded down to a built variant).
 // unpacked: every small pair on a whole wave (the layout for calls with few

@@ -1618,11 +1618,6 @@ lk_status lk_autotune(lk_ctx* ctx, const void* xyz, int dtype, const int64_t* of
   if (crossings) {
     if ((st = sweep(&lk_tuning::segs_per_lane, {2, 4, 8})) != LK_OK) return st;
   } else if (mixed) {
-    // segments per lane and the arctangent's instruction order interact (the
-    // compiler schedules each variant differently): sweep one, the other, and
-    // the first again
-    if ((st = sweep(&lk_tuning::segs_per_lane, {1, 2, 4})) != LK_OK) return st;
-    if ((st = sweep(&lk_tuning::atan_form, {0, 2})) != LK_OK) return st;
     if ((st = sweep(&lk_tuning::segs_per_lane, {1, 2, 4})) != LK_OK) return st;
   } else {
     // FP64: at two segments per lane a batch of one small pair is slow while
@@ -1645,16 +1640,6 @@ lk_status lk_autotune(lk_ctx* ctx, const void* xyz, int dtype, const int64_t* of
         return st;
     } else if ((st = sweep(&lk_tuning::chunk_a, {1024, 2048, 4096, 8192, 16384})) != LK_OK) {
       return st;
-    }
-    if (mixed && !crossings) {
-      // the arctangent form was chosen at the starting chunk; the best form
-      // can change with the chunk (big pairs walk longer per item), so it is
-      // swept again, and the chunk with it when the form changes
-      const int32_t form = cur.atan_form;
-      if ((st = sweep(&lk_tuning::atan_form, {0, 2})) != LK_OK) return st;
-      if (cur.atan_form != form &&
-          (st = sweep(&lk_tuning::chunk_a, {1024, 2048, 4096, 8192, 16384})) != LK_OK)
-        return st;
     }
   }
   if ((st = sweep(&lk_tuning::waves_per_cu, {0, 8, 12})) != LK_OK) return st;
