@@ -9,6 +9,8 @@
 #include <float.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "lk_internal.h"
 
 namespace lk {
@@ -523,266 +525,239 @@ __global__ __launch_bounds__(1024) void scan_k(const int64_t* counts, int64_t n,
 }
 
 // ------------------------------------------------------ potential link search
+// Boxes: W lanes per loop (a power of two up to 64), or a workgroup per loop
+// for few loops, which may be long (below).  Minima and maxima are exact, so
+// they are taken in the input type.  The tiles' pair counts start at 0 here.
 template <typename Tin>
-__global__ __launch_bounds__(256) void boxes_k(const Tin* X, const int64_t* off, int32_t L,
-                                               double* box) {
-  const int lane = threadIdx.x & 63;
-  const int64_t wave = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
-  const int64_t nwaves = ((int64_t)gridDim.x * 256) >> 6;
-  for (int64_t l = wave; l < L; l += nwaves) {
-    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (int64_t v = off[l] + lane; v < off[l + 1]; v += 64)
-      for (int q = 0; q < 3; ++q) {
-        const double x = (double)X[3 * v + q];
-        lo[q] = fmin(lo[q], x);
-        hi[q] = fmax(hi[q], x);
-      }
-    for (int o = 32; o > 0; o >>= 1)
+struct MinMax {
+  Tin lo[3], hi[3];
+  __device__ __forceinline__ void clear() {
+    for (int q = 0; q < 3; ++q) {
+      lo[q] = (Tin)INFINITY;
+      hi[q] = (Tin)-INFINITY;
+    }
+  }
+  __device__ __forceinline__ void add(const Tin* p) {
+    for (int q = 0; q < 3; ++q) {
+      lo[q] = fmin(lo[q], p[q]);
+      hi[q] = fmax(hi[q], p[q]);
+    }
+  }
+  template <int W>
+  __device__ __forceinline__ void reduce() {
+    for (int o = W / 2; o > 0; o >>= 1)
       for (int q = 0; q < 3; ++q) {
         lo[q] = fmin(lo[q], __shfl_xor(lo[q], o));
         hi[q] = fmax(hi[q], __shfl_xor(hi[q], o));
       }
-    if (lane == 0)
-      for (int q = 0; q < 3; ++q) {
-        box[6 * l + q] = lo[q];
-        box[6 * l + 3 + q] = hi[q];
-      }
+  }
+  __device__ __forceinline__ void store(double* b) const {
+    for (int q = 0; q < 3; ++q) {
+      b[q] = (double)lo[q];
+      b[3 + q] = (double)hi[q];
+    }
+  }
+};
+
+__device__ __forceinline__ void clear_tiles(unsigned long long* tiles, int32_t L) {
+  const int32_t n = (L + kRowTile - 1) / kRowTile;
+  for (int32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x)
+    tiles[k] = 0ull;
+}
+
+template <typename Tin, int W>
+__global__ __launch_bounds__(256) void boxes_k(const Tin* X, const int64_t* off, int32_t L,
+                                               double* box, unsigned long long* tiles) {
+  clear_tiles(tiles, L);
+  const int sub = threadIdx.x & (W - 1);
+  const int64_t first = ((int64_t)blockIdx.x * 256 + threadIdx.x) / W;
+  const int64_t stride = (int64_t)gridDim.x * 256 / W;
+  // the same trip count in every lane (the reduction is wavefront-collective)
+  const int64_t trips = (L + stride - 1) / stride;
+  for (int64_t t = 0; t < trips; ++t) {
+    const int64_t l = first + t * stride;
+    MinMax<Tin> m;
+    m.clear();
+    if (l < L)
+      for (int64_t v = off[l] + sub; v < off[l + 1]; v += W) m.add(X + 3 * v);
+    m.template reduce<W>();
+    if (l < L && sub == 0) m.store(box + 6 * l);
   }
 }
 
+template <typename Tin>
+__global__ __launch_bounds__(1024) void boxes_wide_k(const Tin* X, const int64_t* off, int32_t L,
+                                                     double* box, unsigned long long* tiles) {
+  __shared__ MinMax<Tin> part[16];
+  clear_tiles(tiles, L);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  for (int64_t l = blockIdx.x; l < L; l += gridDim.x) {
+    MinMax<Tin> m;
+    m.clear();
+    for (int64_t v = off[l] + threadIdx.x; v < off[l + 1]; v += blockDim.x) m.add(X + 3 * v);
+    m.template reduce<64>();
+    if (lane == 0) part[w] = m;
+    __syncthreads();
+    if (w == 0) {
+      MinMax<Tin> t;
+      t.clear();
+      if (lane < nw) t = part[lane];
+      t.template reduce<16>();
+      if (lane == 0) t.store(box + 6 * l);
+    }
+    __syncthreads();
+  }
+}
+
+// All six bounds are loaded before the first comparison (a chain of || would wait
+// for them one after the other).
 __device__ __forceinline__ bool overlap(const double* P, const double* Q) {
-  return !(P[0] > Q[3] || Q[0] > P[3] || P[1] > Q[4] || Q[1] > P[4] || P[2] > Q[5] || Q[2] > P[5]);
-}
-
-// Thread i scans j > i through LDS tiles of boxes; write = 0 counts, 1 fills.
-template <int WRITE>
-__global__ __launch_bounds__(256) void pair_scan_k(const double* box, int32_t L, int64_t* counts,
-                                                   const int64_t* row_start, int32_t* out,
-                                                   int64_t cap) {
-  __shared__ double tile[256 * 6];
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  double me[6];
-  if (i < L)
-    for (int q = 0; q < 6; ++q) me[q] = box[6 * i + q];
-  int64_t cnt = 0;
-  int64_t pos = (WRITE && i < L) ? row_start[i] : 0;
-  for (int64_t t0 = (int64_t)blockIdx.x * 256; t0 < L; t0 += 256) {
-    __syncthreads();
-    for (int k = threadIdx.x; k < 256 * 6; k += 256) {
-      const int64_t g = t0 * 6 + k;
-      tile[k] = (g < (int64_t)L * 6) ? box[g] : 0.0;
-    }
-    __syncthreads();
-    if (i < L) {
-      const int kend = (L - t0) < 256 ? (int)(L - t0) : 256;
-      for (int k = 0; k < kend; ++k) {
-        const int64_t j = t0 + k;
-        if (j <= i) continue;
-        if (overlap(me, &tile[6 * k])) {
-          if (WRITE) {
-            if (pos < cap) {
-              out[2 * pos] = (int32_t)i;
-              out[2 * pos + 1] = (int32_t)j;
-            }
-            ++pos;
-          } else {
-            ++cnt;
-          }
-        }
-      }
-    }
-  }
-  if (!WRITE && i < L) counts[i] = cnt;
+  const double q0 = Q[0], q1 = Q[1], q2 = Q[2], q3 = Q[3], q4 = Q[4], q5 = Q[5];
+  return !((P[0] > q3) | (q0 > P[3]) | (P[1] > q4) | (q1 > P[4]) | (P[2] > q5) | (q2 > P[5]));
 }
 
 // ------------------------------------- potential link search on a hashed grid
-// A box is "regular" when it is finite and no side is longer than half the
-// cell size h; regular boxes are binned by the cell of their min corner.  Two
-// overlapping regular boxes have min corners at most h/2 apart on every
-// axis, so their cells differ by at most one: a regular box only meets the
-// regular boxes of the 27 cells around its own.  Cells are hashed into a
-// table of buckets, so the scene's extent does not matter; boxes of other
-// cells that share a bucket are candidates the box test rejects.  Every
-// other box (large, empty or non-finite) is tested against all boxes with
-// the same predicate as the brute-force scan, so both give exactly the same
-// pairs.  Each pair is found once, from its smaller index; a row's pairs are
-// sorted by j afterwards, so the output is lexicographic.
-__device__ __forceinline__ bool box_regular(const double* b, double h) {
+// A box is "regular" when it is finite, no side is longer than `side` (the cell
+// size h is 17/16 of that) and its cell coordinates are below 2^40; regular
+// boxes are binned by the cell of their min corner.  Two overlapping regular
+// boxes have min corners at most 16/17 of a cell apart on every axis, so with
+// the rounding of the coordinates (below 2^-11 of a cell) their cells differ
+// by at most one: a regular box only meets the regular boxes of the 27 cells
+// around its own.  (Cells of twice the side gave 3.5 times the candidates on a
+// sheet.)  Cells are hashed into a table of buckets, so the scene's extent does
+// not matter; boxes of other cells that share a bucket are candidates the box
+// test rejects.  Every other box (large, empty, far off or non-finite) is
+// tested against all boxes with the same predicate as the all-pairs scan, so
+// both give exactly the same pairs.  Each pair is found once, from its smaller
+// index; a row's pairs are sorted by j, so the output is lexicographic.
+__device__ __forceinline__ double grid_cell(const GridParams& g, const double* b, int q) {
+  return floor((b[q] - g.lo[q]) * g.inv_h);
+}
+
+__device__ __forceinline__ bool box_regular(const GridParams& g, const double* b) {
   bool ok = true;
   for (int q = 0; q < 3; ++q) {
     const double e = b[3 + q] - b[q];
-    ok = ok && isfinite(b[q]) && isfinite(b[3 + q]) && e >= 0.0 && e <= 0.5 * h;
+    ok = ok && isfinite(b[q]) && isfinite(b[3 + q]) && e >= 0.0 && e <= g.side &&
+         fabs(grid_cell(g, b, q)) < 1.0e12;
   }
   return ok;
 }
 
-__device__ __forceinline__ int64_t grid_coord(const GridParams& g, const double* b, int q) {
-  // far beyond any real scene the coordinate saturates (a shared cell only
-  // adds candidates; boxes that far apart do not overlap a nearer one)
-  const double c = floor((b[q] - g.lo[q]) / g.h);
-  return c < 4.0e18 ? (int64_t)c : (int64_t)4000000000000000000ll;
-}
-
 // buckets is a power of two, so the hash is masked rather than divided
-__device__ __forceinline__ int64_t grid_bucket(const GridParams& g, int64_t x, int64_t y,
+__device__ __forceinline__ int32_t grid_bucket(const GridParams& g, int64_t x, int64_t y,
                                                int64_t z) {
   const uint64_t k = ((uint64_t)x * 73856093ull) ^ ((uint64_t)y * 19349663ull) ^
                      ((uint64_t)z * 83492791ull);
-  return (int64_t)((k ^ (k >> 29)) & (uint64_t)(g.buckets - 1));
+  return (int32_t)((k ^ (k >> 29)) & (uint64_t)(g.buckets - 1));
 }
 
-// The grid parameters in three passes over the boxes; grid_bin_k finishes
-// them from the partials.  Every reduction runs in a fixed order (64 workgroup
-// partials, each a tree in LDS), so the cell size does not depend on
-// scheduling.  Pass 0 sums the box sizes (the largest side per box) and
+// The grid parameters in two passes over the boxes.  Every reduction runs in a
+// fixed order (64 workgroup partials, each a tree in LDS), so the cell size
+// does not depend on scheduling.  Pass 0 sums the box sizes (the largest side
+// per box), takes the least min corner of the boxes with a finite size and
 // clears the bucket counts; pass 1 takes the largest size not above 4 x their
-// mean; pass 2 takes the least min corner of the boxes regular at h = 2 x that
-// largest size.  A box's size and regularity use the same tests everywhere.
+// mean.
 __device__ __forceinline__ double grid_box_size(const double* b) {
   double e = -1.0;
   for (int q = 0; q < 3; ++q) e = fmax(e, b[3 + q] - b[q]);
   return e;
 }
 
-// every thread of every workgroup reduces the partials the same way
-__device__ __forceinline__ double grid_size_cap(const double* part) {
-  double s = 0.0, c = 0.0;
-  for (int k = 0; k < kGridStatBlocks; ++k) {
-    s += part[k];
-    c += part[kGridStatBlocks + k];
-  }
-  return 4.0 * (c > 0.0 ? s / c : 0.0);
+static_assert(kGridStatBlocks == 64, "one partial per lane");
+__device__ __forceinline__ double wave_sum(double v) {
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
 }
-__device__ __forceinline__ double grid_cell_size(const double* part) {
-  double em = 0.0;
-  for (int k = 0; k < kGridStatBlocks; ++k) em = fmax(em, part[2 * kGridStatBlocks + k]);
-  return em > 0.0 ? 2.0 * em : 1.0;
+__device__ __forceinline__ double wave_min(double v) {
+  for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o));
+  return v;
+}
+__device__ __forceinline__ double wave_max(double v) {
+  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
+  return v;
 }
 
 template <int PASS>
-__global__ __launch_bounds__(256) void grid_stats_k(const double* box, int32_t L,
-                                                    int64_t buckets, double* part,
-                                                    unsigned long long* cell_count,
-                                                    int32_t* n_over) {
-  __shared__ double red[3][256];
-  const int t = threadIdx.x;
-  const double cap = PASS == 1 ? grid_size_cap(part) : 0.0;
-  const double h = PASS == 2 ? grid_cell_size(part) : 0.0;
-  double v[3] = {0.0, 0.0, 0.0};
-  if (PASS == 2) v[0] = v[1] = v[2] = INFINITY;
+__global__ __launch_bounds__(256) void grid_stats_k(const double* box, int32_t L, int64_t buckets,
+                                                    double* part, uint32_t* cell_count,
+                                                    int32_t* n_over, uint32_t* n_binned) {
+  __shared__ double red[5][256];
+  const int t = threadIdx.x, lane = t & 63;
+  double cap = 0.0;
+  if (PASS == 1) {
+    const double s = wave_sum(part[lane]), c = wave_sum(part[kGridStatBlocks + lane]);
+    cap = 4.0 * (c > 0.0 ? s / c : 0.0);
+  }
+  double v[5] = {0.0, 0.0, INFINITY, INFINITY, INFINITY};
   for (int64_t i = (int64_t)blockIdx.x * 256 + t; i < L; i += kGridStatBlocks * 256) {
     const double* b = box + 6 * i;
+    const double e = grid_box_size(b);
     if (PASS == 0) {
-      const double e = grid_box_size(b);
       if (isfinite(e) && e >= 0.0) {
         v[0] += e;
         v[1] += 1.0;
+        for (int q = 0; q < 3; ++q)
+          if (isfinite(b[q])) v[2 + q] = fmin(v[2 + q], b[q]);
       }
-    } else if (PASS == 1) {
-      const double e = grid_box_size(b);
-      if (isfinite(e) && e <= cap) v[0] = fmax(v[0], e);
-    } else if (box_regular(b, h)) {
-      for (int q = 0; q < 3; ++q) v[q] = fmin(v[q], b[q]);
+    } else if (isfinite(e) && e <= cap) {
+      v[0] = fmax(v[0], e);
     }
   }
   if (PASS == 0) {
     for (int64_t k = (int64_t)blockIdx.x * 256 + t; k < buckets; k += kGridStatBlocks * 256)
-      cell_count[k] = 0ull;
-    if (blockIdx.x == 0 && t == 0) *n_over = 0;
+      cell_count[k] = 0u;
+    if (blockIdx.x == 0 && t == 0) {
+      *n_over = 0;
+      *n_binned = 0u;
+    }
   }
-  for (int q = 0; q < 3; ++q) red[q][t] = v[q];
+  for (int q = 0; q < 5; ++q) red[q][t] = v[q];
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
     if (t < w) {
       if (PASS == 0) {
         red[0][t] += red[0][t + w];
         red[1][t] += red[1][t + w];
-      } else if (PASS == 1) {
-        red[0][t] = fmax(red[0][t], red[0][t + w]);
+        for (int q = 2; q < 5; ++q) red[q][t] = fmin(red[q][t], red[q][t + w]);
       } else {
-        for (int q = 0; q < 3; ++q) red[q][t] = fmin(red[q][t], red[q][t + w]);
+        red[0][t] = fmax(red[0][t], red[0][t + w]);
       }
     }
     __syncthreads();
   }
   if (t == 0) {
-    if (PASS == 0) {
-      part[blockIdx.x] = red[0][0];
-      part[kGridStatBlocks + blockIdx.x] = red[1][0];
-    } else if (PASS == 1) {
+    if (PASS == 0)
+      for (int q = 0; q < 5; ++q) part[(q < 2 ? q : q + 1) * kGridStatBlocks + blockIdx.x] = red[q][0];
+    else
       part[2 * kGridStatBlocks + blockIdx.x] = red[0][0];
-    } else {
-      for (int q = 0; q < 3; ++q) part[(3 + q) * kGridStatBlocks + blockIdx.x] = red[q][0];
-    }
   }
 }
 
-__device__ GridParams grid_params_of(const double* part, int64_t buckets) {
+// Each workgroup finishes the grid parameters from the partials; the first one
+// stores them for the later kernels.
+__global__ __launch_bounds__(256) void grid_bin_k(const double* box, int32_t L, const double* part,
+                                                  int64_t buckets, GridParams* gp,
+                                                  uint32_t* cell_count, int32_t* cell_of,
+                                                  int32_t* over, int32_t* n_over) {
+  const int lane = threadIdx.x & 63;
   GridParams g;
-  g.h = grid_cell_size(part);
+  const double em = wave_max(part[2 * kGridStatBlocks + lane]);
+  g.side = em > 0.0 ? em : 1.0;
+  g.inv_h = 1.0 / (1.0625 * g.side);
   for (int q = 0; q < 3; ++q) {
-    double m = INFINITY;
-    for (int k = 0; k < kGridStatBlocks; ++k) m = fmin(m, part[(3 + q) * kGridStatBlocks + k]);
+    const double m = wave_min(part[(3 + q) * kGridStatBlocks + lane]);
     g.lo[q] = isfinite(m) ? m : 0.0;
   }
   g.buckets = buckets;
-  return g;
-}
-
-// Exclusive scan across workgroups of 4096 entries: the tiles' totals, a
-// single-workgroup scan of those into tile offsets (whose last entry is the
-// grand total), then each tile's scan from its offset.
-__global__ __launch_bounds__(1024) void tile_sums_k(const int64_t* counts, int64_t n,
-                                                    int64_t* tile_sum) {
-  __shared__ int64_t wsum[16];
-  const int64_t k0 = (int64_t)blockIdx.x * 4096 + 4 * (int64_t)threadIdx.x;
-  int64_t v = 0;
-  for (int i = 0; i < 4; ++i) v += (k0 + i < n) ? counts[k0 + i] : 0;
-  int64_t tot = 0;
-  block_excl_scan(v, wsum, &tot);
-  if (threadIdx.x == 0) tile_sum[blockIdx.x] = tot;
-}
-
-__global__ __launch_bounds__(1024) void tile_scan_k(const int64_t* counts, int64_t n,
-                                                    const int64_t* tile_off, int64_t* prefix) {
-  __shared__ int64_t wsum[16];
-  const int64_t k0 = (int64_t)blockIdx.x * 4096 + 4 * (int64_t)threadIdx.x;
-  int64_t v[4], sum = 0;
-  for (int i = 0; i < 4; ++i) {
-    v[i] = (k0 + i < n) ? counts[k0 + i] : 0;
-    sum += v[i];
-  }
-  int64_t tot = 0;
-  int64_t run = tile_off[blockIdx.x] + block_excl_scan(sum, wsum, &tot);
-  for (int i = 0; i < 4; ++i) {
-    if (k0 + i < n) prefix[k0 + i] = run;
-    run += v[i];
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) prefix[n] = tile_off[gridDim.x];
-}
-
-// Each workgroup finishes the grid parameters from the partials (the same
-// fixed order everywhere); the first one stores them for the later kernels.
-__global__ __launch_bounds__(256) void grid_bin_k(const double* box, int32_t L,
-                                                  const double* part, int64_t buckets,
-                                                  GridParams* gp,
-                                                  unsigned long long* cell_count,
-                                                  int64_t* cell_of, int32_t* over,
-                                                  int32_t* n_over) {
-  __shared__ GridParams gs;
-  if (threadIdx.x == 0) {
-    gs = grid_params_of(part, buckets);
-    if (blockIdx.x == 0) *gp = gs;
-  }
-  __syncthreads();
-  const GridParams g = gs;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *gp = g;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < L; i += (int64_t)gridDim.x * 256) {
     const double* b = box + 6 * i;
-    if (box_regular(b, g.h)) {
-      const int64_t c =
-          grid_bucket(g, grid_coord(g, b, 0), grid_coord(g, b, 1), grid_coord(g, b, 2));
+    if (box_regular(g, b)) {
+      const int32_t c = grid_bucket(g, (int64_t)grid_cell(g, b, 0), (int64_t)grid_cell(g, b, 1),
+                                    (int64_t)grid_cell(g, b, 2));
       cell_of[i] = c;
-      atomicAdd(&cell_count[c], 1ull);
+      atomicAdd(&cell_count[c], 1u);
     } else {
       cell_of[i] = -1;
       over[atomicAdd(n_over, 1)] = (int32_t)i;
@@ -790,107 +765,226 @@ __global__ __launch_bounds__(256) void grid_bin_k(const double* box, int32_t L,
   }
 }
 
-// cell_count still holds the counts: each box takes a slot by counting down;
-// a copy of the box goes with it, so a bucket's boxes are read contiguously.
+// Room for every bucket's boxes: buckets in order within a workgroup's 1,024,
+// the workgroups' runs in any order (rows are sorted in the end).
+__global__ __launch_bounds__(256) void grid_alloc_k(const uint32_t* cell_count, int64_t buckets,
+                                                    uint2* cell, uint32_t* n_binned) {
+  __shared__ uint32_t wsum[4], base;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t k0 = (int64_t)blockIdx.x * 1024 + 4 * (int64_t)threadIdx.x;
+  uint32_t c[4], sum = 0u;
+  for (int i = 0; i < 4; ++i) {
+    c[i] = k0 + i < buckets ? cell_count[k0 + i] : 0u;
+    sum += c[i];
+  }
+  uint32_t x = sum;
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = __shfl_up(x, o);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) wsum[w] = x;
+  __syncthreads();
+  if (threadIdx.x == 0) base = atomicAdd(n_binned, wsum[0] + wsum[1] + wsum[2] + wsum[3]);
+  __syncthreads();
+  uint32_t run = base + x - sum;
+  for (int q = 0; q < w; ++q) run += wsum[q];
+  for (int i = 0; i < 4; ++i) {
+    if (k0 + i < buckets) cell[k0 + i] = uint2{run, run};
+    run += c[i];
+  }
+}
+
+// Each box takes the next place of its bucket (whose .y ends at the bucket's
+// end); a copy of the box goes with it, so a bucket's boxes are read
+// contiguously.
 __global__ __launch_bounds__(256) void grid_scatter_k(const double* box, int32_t L,
-                                                      const int64_t* cell_of,
-                                                      const int64_t* cell_start,
-                                                      unsigned long long* cell_count,
+                                                      const int32_t* cell_of, uint2* cell,
                                                       int32_t* cell_items, double* cell_box) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < L; i += (int64_t)gridDim.x * 256) {
-    const int64_t c = cell_of[i];
+    const int32_t c = cell_of[i];
     if (c < 0) continue;
-    const unsigned long long k = atomicAdd(&cell_count[c], ~0ull);  // - 1
-    const int64_t pos = cell_start[c] + (int64_t)k - 1;
+    const int64_t pos = atomicAdd(&cell[c].y, 1u);
     cell_items[pos] = (int32_t)i;
     for (int q = 0; q < 6; ++q) cell_box[6 * pos + q] = box[6 * i + q];
   }
 }
 
-// Row i: the pairs (i, j > i), one wavefront per row, the lanes testing
-// candidates side by side.  WRITE = 0 counts, 1 fills (in bucket order for a
-// regular box; ascending j for the others, since each chunk of 64 is emitted
-// in lane order).
-template <int WRITE>
-__global__ __launch_bounds__(256) void grid_rows_k(const double* box, int32_t L,
-                                                   const GridParams* gp, const int64_t* cell_of,
-                                                   const int64_t* cell_start,
-                                                   const int32_t* cell_items,
-                                                   const double* cell_box, const int32_t* over,
-                                                   const int32_t* n_over, int64_t* counts,
-                                                   const int64_t* row_start, int32_t* out) {
-  const GridParams g = *gp;
-  const int32_t no = *n_over;
+// The rows of the pair list, one wavefront per row i, the lanes testing 64
+// candidates j > i side by side; emit(hit, j) is called by all lanes.  GRID:
+// a regular box's candidates are its 27 buckets' boxes as one list (lane t < 27
+// reads bucket t's range, a scan makes the ranges one, and lane c of a round
+// finds its place in it), so a row waits for five loads in turn, not for three
+// in each bucket.  Everything else is tested against all later boxes.
+template <bool GRID, typename Emit>
+__device__ __forceinline__ void row_candidates(const double* box, int32_t L, int64_t i,
+                                               const RowGrid& R, const Emit& emit) {
   const int lane = threadIdx.x & 63;
-  const unsigned long long below = lane ? (~0ull >> (64 - lane)) : 0ull;
-  const int64_t wave = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
-  const int64_t nwaves = ((int64_t)gridDim.x * 256) >> 6;
-  for (int64_t i = wave; i < L; i += nwaves) {
-    double me[6];
-    for (int q = 0; q < 6; ++q) me[q] = box[6 * i + q];
-    int64_t pos = WRITE ? row_start[i] : 0;  // uniform over the wave
-    // all lanes call it; lane with `hit` writes (i, j) in lane order
-    auto emit = [&](bool hit, int64_t j) {
-      const unsigned long long m = __ballot(hit);
-      if (WRITE && hit) {
-        const int64_t at = pos + __popcll(m & below);
-        out[2 * at] = (int32_t)i;
-        out[2 * at + 1] = (int32_t)j;
-      }
-      pos += __popcll(m);
-    };
-    if (cell_of[i] >= 0) {
-      const int64_t c0 = grid_coord(g, me, 0), c1 = grid_coord(g, me, 1), c2 = grid_coord(g, me, 2);
-      // lane t < 27 hashes neighbour cell t; a bucket reached by two
-      // neighbour cells is visited once (at its first lane)
-      const int tl = lane < 27 ? lane : 0;
-      const int64_t mine = grid_bucket(g, c0 + tl % 3 - 1, c1 + (tl / 3) % 3 - 1, c2 + tl / 9 - 1);
-      bool dup = false;
-      for (int u = 0; u < 27; ++u) {
-        const int64_t bu = __shfl(mine, u);
-        dup = dup || (u < lane && bu == mine);
-      }
-      const unsigned long long visit = __ballot(lane < 27 && !dup);
-      for (int t = 0; t < 27; ++t) {
-        if (!((visit >> t) & 1ull)) continue;
-        const int64_t c = __shfl(mine, t);
-        for (int64_t k0 = cell_start[c]; k0 < cell_start[c + 1]; k0 += 64) {
-          const int64_t k = k0 + lane;
-          const bool in = k < cell_start[c + 1];
-          const int32_t j = in ? cell_items[k] : -1;
-          emit(in && j > i && overlap(me, cell_box + 6 * k), j);
-        }
-      }
-      for (int32_t k0 = 0; k0 < no; k0 += 64) {
-        const int32_t k = k0 + lane;
-        const int32_t j = k < no ? over[k] : -1;
-        emit(k < no && j > i && overlap(me, box + 6 * (int64_t)j), j);
-      }
-    } else {
-      for (int64_t j0 = i + 1; j0 < L; j0 += 64) {
-        const int64_t j = j0 + lane;
-        emit(j < L && overlap(me, box + 6 * (j < L ? j : 0)), j);
-      }
+  double me[6];
+  for (int q = 0; q < 6; ++q) me[q] = box[6 * i + q];
+  if (GRID && R.cell_of[i] >= 0) {
+    const GridParams g = *R.params;
+    const int64_t c0 = (int64_t)grid_cell(g, me, 0), c1 = (int64_t)grid_cell(g, me, 1),
+                  c2 = (int64_t)grid_cell(g, me, 2);
+    const int tl = lane < 27 ? lane : 0;
+    const int32_t mine = grid_bucket(g, c0 + tl % 3 - 1, c1 + (tl / 3) % 3 - 1, c2 + tl / 9 - 1);
+    // a bucket reached by two neighbour cells is visited once, at its first lane
+    bool dup = lane >= 27;
+    for (int u = 0; u < 26; ++u)
+      dup = dup || (u < lane && __builtin_amdgcn_readlane(mine, u) == mine);
+    const uint2 se = dup ? uint2{0u, 0u} : R.cell[mine];
+    const int32_t n = (int32_t)(se.y - se.x);
+    int32_t x = n;
+    for (int o = 1; o < 32; o <<= 1) {
+      const int32_t y = __shfl_up(x, o);
+      if (lane >= o) x += y;
     }
-    if (!WRITE && lane == 0) counts[i] = pos;
+    const int32_t total = __builtin_amdgcn_readlane(x, 26), before = x - n;
+    const int32_t shift = (int32_t)se.x - before;  // a bucket's place of list entry k: k + shift
+    const unsigned long long some = __ballot(n > 0);
+    for (int32_t k0 = 0; k0 < total; k0 += 64) {
+      const int32_t k = k0 + lane;
+      int32_t sh = 0;
+      for (unsigned long long m = some; m; m &= m - 1ull) {
+        const int u = __ffsll((long long)m) - 1;
+        sh = k >= __builtin_amdgcn_readlane(before, u) ? __builtin_amdgcn_readlane(shift, u) : sh;
+      }
+      const bool in = k < total;
+      const int64_t at = in ? (int64_t)k + sh : 0;
+      const int32_t j = in ? R.cell_items[at] : -1;
+      emit(overlap(me, R.cell_box + 6 * at) & (j > i), j);  // (j is -1 beyond the list)
+    }
+    const int32_t no = *R.n_over;
+    for (int32_t k0 = 0; k0 < no; k0 += 64) {
+      const int32_t k = k0 + lane;
+      const int32_t j = k < no ? R.over[k] : -1;
+      emit(k < no && j > i && overlap(me, box + 6 * (int64_t)j), j);
+    }
+  } else {
+    for (int64_t j0 = i + 1; j0 < L; j0 += 256) {
+      bool hit[4];  // four rounds' loads in flight
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int64_t j = j0 + 64 * q + lane;
+        hit[q] = overlap(me, box + 6 * (j < L ? j : i)) & (j < L);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) emit(hit[q], (int32_t)(j0 + 64 * q + lane));
+    }
   }
 }
 
-// Rows of regular boxes were filled in cell order: sort each by j.
-__global__ __launch_bounds__(256) void grid_sort_rows_k(int32_t L, const int64_t* cell_of,
-                                                        const int64_t* row_start, int32_t* out) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < L; i += (int64_t)gridDim.x * 256) {
-    if (cell_of[i] < 0) continue;
-    const int64_t a = row_start[i], b = row_start[i + 1];
-    for (int64_t k = a + 1; k < b; ++k) {
-      const int32_t v = out[2 * k + 1];
-      int64_t m = k - 1;
-      while (m >= a && out[2 * m + 1] > v) {
-        out[2 * (m + 1) + 1] = out[2 * m + 1];
-        --m;
+// Counts the rows' pairs, per row and per tile of kRowTile rows, and keeps the
+// first kRowSlots of each row for the fill.  16 rows per workgroup, whose sum
+// goes to the tile in one atomic (one per row queued 256 of them on each
+// tile's count: 104 us instead of 43 for 20,000 loops).
+template <bool GRID>
+__global__ __launch_bounds__(64 * kFillRows) void rows_count_k(const double* box, int32_t L,
+                                                               RowGrid R, RowBufs B) {
+  __shared__ int32_t sum[kFillRows];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const unsigned long long below = lane ? (~0ull >> (64 - lane)) : 0ull;
+  const int64_t i = (int64_t)blockIdx.x * kFillRows + w;
+  int32_t cnt = 0;  // uniform over the wave
+  if (i < L) {
+    row_candidates<GRID>(box, L, i, R, [&](bool hit, int32_t j) {
+      const unsigned long long m = __ballot(hit);
+      const int32_t at = cnt + (int32_t)__popcll(m & below);
+      if (hit && at < kRowSlots) B.slots[i * kRowSlots + at] = j;
+      cnt += (int32_t)__popcll(m);
+    });
+    if (lane == 0) B.counts[i] = cnt;
+  }
+  if (lane == 0) sum[w] = cnt;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned long long t = 0ull;
+    for (int q = 0; q < kFillRows; ++q) t += (unsigned long long)sum[q];
+    if (t) atomicAdd(&B.tiles[(int64_t)blockIdx.x * kFillRows / kRowTile], t);
+  }
+}
+
+// Writes the rows, 16 per workgroup.  A row's place is the sum of the earlier
+// tiles and of its tile's earlier rows, which each workgroup adds up itself
+// (cheaper than a scan in a launch of its own).  Nothing is written unless all
+// pairs fit; the first workgroup reports the total to the host.  A row whose
+// pairs are all in its slots is sorted by counting, lane against lane; a longer
+// one is searched again, and one lane sorts it in place if the grid gave it.
+template <bool GRID>
+__global__ __launch_bounds__(256) void rows_fill_k(const double* box, int32_t L, RowGrid R,
+                                                   RowBufs B, int32_t* out, int64_t capacity,
+                                                   int64_t* host_total) {
+  __shared__ int64_t red[2][4];
+  __shared__ int32_t row_n[kFillRows];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t base = (int64_t)blockIdx.x * kFillRows;
+  const int64_t tile = base / kRowTile, n_tiles = (L + kRowTile - 1) / kRowTile;
+  int64_t before = 0, total = 0;
+  for (int64_t k = threadIdx.x; k < n_tiles; k += 256) {
+    const int64_t c = (int64_t)B.tiles[k];
+    total += c;
+    if (k < tile) before += c;
+  }
+  const int64_t r = tile * kRowTile + threadIdx.x;  // kRowTile == 256
+  const int32_t c = r < L ? B.counts[r] : 0;
+  if (r < base) before += c;
+  if (r >= base && r < base + kFillRows) row_n[r - base] = c;
+  for (int o = 32; o > 0; o >>= 1) {
+    before += __shfl_xor(before, o);
+    total += __shfl_xor(total, o);
+  }
+  if (lane == 0) {
+    red[0][w] = before;
+    red[1][w] = total;
+  }
+  __syncthreads();
+  total = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+    __hip_atomic_store(host_total, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (total > capacity) return;
+  int64_t pos = red[0][0] + red[0][1] + red[0][2] + red[0][3];
+  const unsigned long long below = lane ? (~0ull >> (64 - lane)) : 0ull;
+  for (int q = 0; q < kFillRows; ++q) {
+    const int64_t i = base + q;
+    const int32_t n = __builtin_amdgcn_readfirstlane(row_n[q]);
+    if ((q & 3) == w && i < L && n > 0) {
+      if (n <= kRowSlots) {
+        const int32_t j = lane < n ? B.slots[i * kRowSlots + lane] : 0;
+        int32_t rank = lane;
+        if (GRID) {
+          rank = 0;
+          for (int u = 0; u < n; ++u) rank += __builtin_amdgcn_readlane(j, u) < j ? 1 : 0;
+        }
+        if (lane < n) {
+          out[2 * (pos + rank)] = (int32_t)i;
+          out[2 * (pos + rank) + 1] = j;
+        }
+      } else {
+        int64_t to = pos;  // uniform over the wave
+        row_candidates<GRID>(box, L, i, R, [&](bool hit, int32_t j) {
+          const unsigned long long m = __ballot(hit);
+          if (hit) {
+            const int64_t at = to + __popcll(m & below);
+            out[2 * at] = (int32_t)i;
+            out[2 * at + 1] = j;
+          }
+          to += __popcll(m);
+        });
+        if (GRID && R.cell_of[i] >= 0) {
+          __threadfence_block();
+          if (lane == 0)
+            for (int64_t k = pos + 1; k < pos + n; ++k) {
+              const int32_t v = out[2 * k + 1];
+              int64_t m = k - 1;
+              while (m >= pos && out[2 * m + 1] > v) {
+                out[2 * (m + 1) + 1] = out[2 * m + 1];
+                --m;
+              }
+              out[2 * (m + 1) + 1] = v;
+            }
+        }
       }
-      out[2 * (m + 1) + 1] = v;
     }
+    pos += n;
   }
 }
 
@@ -1104,63 +1198,56 @@ hipError_t launch_scan(const int64_t* counts, int64_t n, int64_t* prefix, hipStr
   return hipGetLastError();
 }
 
+// A workgroup per loop below 2,048 loops (of 1,024 threads below 256, where
+// loops may be long: 100 knit rows of 8,000 vertices took 77 us with a
+// wavefront each, 14 us so), a wavefront per loop below 8,192, 16 lanes above
+// (20,000 loops of 32 vertices: 19.8 us with a wavefront each, 5.6 us so).
 hipError_t launch_boxes(const void* xyz, bool in_f64, const int64_t* off, int32_t n_loops,
-                        double* boxes, hipStream_t s) {
-  const int lb = blocks_for((int64_t)n_loops * 64, 256, 8192);
+                        double* boxes, unsigned long long* tiles, hipStream_t s) {
+  auto go = [&](auto* X) {
+    using Tin = std::remove_const_t<std::remove_pointer_t<decltype(X)>>;
+    if (n_loops < 2048)
+      boxes_wide_k<Tin><<<n_loops, n_loops < 256 ? 1024 : 128, 0, s>>>(X, off, n_loops, boxes, tiles);
+    else if (n_loops < 8192)
+      boxes_k<Tin, 64><<<blocks_for((int64_t)n_loops * 64, 256, 8192), 256, 0, s>>>(X, off, n_loops,
+                                                                                    boxes, tiles);
+    else
+      boxes_k<Tin, 16><<<blocks_for((int64_t)n_loops * 16, 256, 8192), 256, 0, s>>>(X, off, n_loops,
+                                                                                    boxes, tiles);
+  };
   if (in_f64)
-    boxes_k<double><<<lb, 256, 0, s>>>((const double*)xyz, off, n_loops, boxes);
+    go((const double*)xyz);
   else
-    boxes_k<float><<<lb, 256, 0, s>>>((const float*)xyz, off, n_loops, boxes);
+    go((const float*)xyz);
   return hipGetLastError();
 }
 
-hipError_t launch_pair_count(const double* boxes, int32_t n_loops, int64_t* counts,
-                             hipStream_t s) {
-  pair_scan_k<0><<<blocks_for(n_loops, 256), 256, 0, s>>>(boxes, n_loops, counts, nullptr, nullptr,
-                                                          0);
-  return hipGetLastError();
-}
-
-hipError_t launch_pair_fill(const double* boxes, int32_t n_loops, const int64_t* row_start,
-                            int32_t* pairs_out, int64_t capacity, hipStream_t s) {
-  pair_scan_k<1><<<blocks_for(n_loops, 256), 256, 0, s>>>(boxes, n_loops, nullptr, row_start,
-                                                          pairs_out, capacity);
-  return hipGetLastError();
-}
-
-hipError_t launch_grid_pairs(const double* boxes, int32_t n_loops, const GridBufs& b, int pass,
-                             const int64_t* row_start, int32_t* pairs_out, hipStream_t s) {
+hipError_t launch_grid(const double* boxes, int32_t n_loops, const GridBufs& b, hipStream_t s) {
   const int g = blocks_for(n_loops, 256, 4096);
-  const int gw = blocks_for((int64_t)n_loops * 64, 256, 16384);  // one wavefront per row
-  switch (pass) {
-    case 0: {  // grid, binning and the per-cell scan
-      grid_stats_k<0><<<kGridStatBlocks, 256, 0, s>>>(boxes, n_loops, b.buckets, b.part,
-                                                      b.cell_count, b.n_over);
-      grid_stats_k<1><<<kGridStatBlocks, 256, 0, s>>>(boxes, n_loops, b.buckets, b.part,
-                                                      nullptr, nullptr);
-      grid_stats_k<2><<<kGridStatBlocks, 256, 0, s>>>(boxes, n_loops, b.buckets, b.part,
-                                                      nullptr, nullptr);
-      grid_bin_k<<<g, 256, 0, s>>>(boxes, n_loops, b.part, b.buckets, b.params, b.cell_count,
-                                   b.cell_of, b.over, b.n_over);
-      const int64_t nt = (b.buckets + 4095) / 4096;
-      const int64_t* counts = reinterpret_cast<const int64_t*>(b.cell_count);
-      tile_sums_k<<<(unsigned)nt, 1024, 0, s>>>(counts, b.buckets, b.tiles);
-      scan_k<<<1, 1024, 0, s>>>(b.tiles, nt, b.tiles + nt + 1);
-      tile_scan_k<<<(unsigned)nt, 1024, 0, s>>>(counts, b.buckets, b.tiles + nt + 1,
-                                                b.cell_start);
-      grid_scatter_k<<<g, 256, 0, s>>>(boxes, n_loops, b.cell_of, b.cell_start, b.cell_count,
-                                       b.cell_items, b.cell_box);
-      grid_rows_k<0><<<gw, 256, 0, s>>>(boxes, n_loops, b.params, b.cell_of, b.cell_start,
-                                       b.cell_items, b.cell_box, b.over, b.n_over, b.row_counts,
-                                       nullptr, nullptr);
-      break;
-    }
-    default:  // fill and sort the rows
-      grid_rows_k<1><<<gw, 256, 0, s>>>(boxes, n_loops, b.params, b.cell_of, b.cell_start,
-                                       b.cell_items, b.cell_box, b.over, b.n_over, nullptr,
-                                       row_start, pairs_out);
-      grid_sort_rows_k<<<g, 256, 0, s>>>(n_loops, b.cell_of, row_start, pairs_out);
-      break;
+  grid_stats_k<0><<<kGridStatBlocks, 256, 0, s>>>(boxes, n_loops, b.buckets, b.part, b.cell_count,
+                                                  b.rows.n_over, b.n_binned);
+  grid_stats_k<1><<<kGridStatBlocks, 256, 0, s>>>(boxes, n_loops, b.buckets, b.part, nullptr,
+                                                  nullptr, nullptr);
+  grid_bin_k<<<g, 256, 0, s>>>(boxes, n_loops, b.part, b.buckets, b.rows.params, b.cell_count,
+                               b.rows.cell_of, b.rows.over, b.rows.n_over);
+  grid_alloc_k<<<(unsigned)((b.buckets + 1023) / 1024), 256, 0, s>>>(b.cell_count, b.buckets,
+                                                                     b.rows.cell, b.n_binned);
+  grid_scatter_k<<<g, 256, 0, s>>>(boxes, n_loops, b.rows.cell_of, b.rows.cell, b.rows.cell_items,
+                                   b.rows.cell_box);
+  return hipGetLastError();
+}
+
+hipError_t launch_pair_rows(const double* boxes, int32_t n_loops, const RowGrid* grid,
+                            const RowBufs& b, int32_t* pairs_out, int64_t capacity,
+                            int64_t* host_total, hipStream_t s) {
+  const unsigned gf = (unsigned)(((int64_t)n_loops + kFillRows - 1) / kFillRows);
+  if (grid) {
+    rows_count_k<true><<<gf, 64 * kFillRows, 0, s>>>(boxes, n_loops, *grid, b);
+    rows_fill_k<true><<<gf, 256, 0, s>>>(boxes, n_loops, *grid, b, pairs_out, capacity, host_total);
+  } else {
+    rows_count_k<false><<<gf, 64 * kFillRows, 0, s>>>(boxes, n_loops, RowGrid{}, b);
+    rows_fill_k<false><<<gf, 256, 0, s>>>(boxes, n_loops, RowGrid{}, b, pairs_out, capacity,
+                                          host_total);
   }
   return hipGetLastError();
 }

@@ -383,41 +383,51 @@ hipError_t launch_finalize_replan(const Sched& s, const unsigned long long* acc,
 hipError_t launch_zero_i64(int64_t* p, hipStream_t s);
 // Exclusive scan of counts[0..n) into prefix[0..n] (single workgroup).
 hipError_t launch_scan(const int64_t* counts, int64_t n, int64_t* prefix, hipStream_t s);
-// Potential link search.
+// Potential link search: boxes (also clears the tiles' pair counts), the grid
+// (optional), then the rows of the pair list.
 hipError_t launch_boxes(const void* xyz, bool in_f64, const int64_t* off, int32_t n_loops,
-                        double* boxes /*[n_loops][6]*/, hipStream_t s);
-hipError_t launch_pair_count(const double* boxes, int32_t n_loops, int64_t* counts,
-                             hipStream_t s);
-hipError_t launch_pair_fill(const double* boxes, int32_t n_loops, const int64_t* row_start,
-                            int32_t* pairs_out, int64_t capacity, hipStream_t s);
+                        double* boxes /*[n_loops][6]*/, unsigned long long* tiles, hipStream_t s);
 
-// Potential link search on a hashed grid of the boxes' min corners (see
-// grid_stats_k): the same pairs as launch_pair_count / launch_pair_fill in
-// about L x (boxes in 27 buckets) tests instead of L^2 / 2.
+// Rows of the pair list: pairs per row and per tile of kRowTile rows, and each
+// row's first kRowSlots second indices.
+constexpr int kRowTile = 256, kRowSlots = 32, kFillRows = 16;
+struct RowBufs {
+  int32_t* counts;            // [L]
+  unsigned long long* tiles;  // [ceil(L / kRowTile)]
+  int32_t* slots;             // [L][kRowSlots]
+};
+
+// A hashed grid of the boxes' min corners (see grid_stats_k): the same pairs as
+// without it in about L x (boxes in 27 buckets) tests instead of L^2 / 2.
 struct GridParams {
-  double h;         // cell size; boxes with every side at most h / 2 are binned
+  double side;      // boxes with every side at most this are binned
+  double inv_h;     // 1 / the cell size
   double lo[3];     // grid origin
   int64_t buckets;  // hash table size (a power of two)
 };
-struct GridBufs {
+struct RowGrid {  // what the rows read of it
   GridParams* params;
-  unsigned long long* cell_count;  // [buckets] (int64 counts)
-  int64_t* cell_start;             // [buckets + 1]
-  int64_t* cell_of;                // [L] bucket, -1 for a box tested against all
-  int32_t* cell_items;             // [L]
-  double* cell_box;                // [L][6] the boxes in bucket order
-  int32_t* over;                   // [L]
+  int32_t* cell_of;     // [L] bucket, -1 for a box tested against all
+  uint2* cell;          // [buckets] first and end place of a bucket's boxes
+  int32_t* cell_items;  // [L] box ids by place
+  double* cell_box;     // [L][6] the boxes by place
+  int32_t* over;        // [L] the boxes tested against all
   int32_t* n_over;
-  int64_t* row_counts;             // [L]
-  double* part;                    // [kGridStatBlocks][6] per-workgroup partials
-  int64_t* tiles;                  // [2 (buckets / 4096 + 2)] tile sums and offsets
-  int64_t buckets;
+};
+struct GridBufs {
+  RowGrid rows;
+  uint32_t* cell_count;  // [buckets]
+  uint32_t* n_binned;
+  double* part;          // [kGridStatBlocks][6] per-workgroup partials
+  int64_t buckets;       // at most 2^31
 };
 constexpr int kGridStatBlocks = 64;
-// pass 0: grid, binning, per-row counts into row_counts; pass 1 (after the
-// caller's scan of the counts into row_start): fill and sort the rows.
-hipError_t launch_grid_pairs(const double* boxes, int32_t n_loops, const GridBufs& b, int pass,
-                             const int64_t* row_start, int32_t* pairs_out, hipStream_t s);
+hipError_t launch_grid(const double* boxes, int32_t n_loops, const GridBufs& b, hipStream_t s);
+// Counts, then fills pairs_out if all fit `capacity` (else writes nothing);
+// *host_total (host memory the device can write) receives the count.
+hipError_t launch_pair_rows(const double* boxes, int32_t n_loops, const RowGrid* grid,
+                            const RowBufs& b, int32_t* pairs_out, int64_t capacity,
+                            int64_t* host_total, hipStream_t s);
 
 // Verification: per merged position, mismatch flags, then a scan and a scatter.
 hipError_t launch_verify(const int32_t* pairs, const int32_t* lk, int64_t n,

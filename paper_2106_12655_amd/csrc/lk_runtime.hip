@@ -71,6 +71,7 @@ struct lk_ctx {
   // workspace
   DevBuf loop_flags, minseg2, xi, recs, big_prefix, meta, acc, flags, refit_list;
   DevBuf boxes, vcounts, vprefix;
+  DevBuf pls_rows;  // pair search: per-row and per-tile counts, the rows' first hits
   DevBuf cc_blk, cc_sup;  // crossing count: projected block and superblock boxes
   DevBuf bh_nodes, bh_lists, bh_counts;  // Barnes-Hut trees, node-pair lists, counts
   DevBuf bh_adapt;  // adaptive beta: per-pair error estimate (fixed point) and beta
@@ -87,6 +88,9 @@ struct lk_ctx {
   bool bh_adaptive = false;      // Sec. 3.4.4's second evaluation at a larger beta
   double bh_beta_max = 10.0;
   double bh_target = 0.2;
+  // counts that a kernel writes for the host to read after a synchronisation
+  // (pinned; calls on one context do not overlap)
+  int64_t* host_total = nullptr;
   uint64_t ws_epoch = 0;  // bumped whenever a workspace buffer moves
   // completion of the context's last enqueued work (calls on one context do
   // not overlap, so it covers every earlier call): a buffer that grows waits
@@ -669,6 +673,59 @@ lk_status bh_prepare(lk_ctx* ctx, const int64_t* off, int32_t n_loops, int64_t n
   return ensure(ctx, ctx->bh_counts, 4 * (size_t)(lk::kBhMaxIters + 3));
 }
 
+// ------------------------------------------------------- pair search buffers
+// From this many loops on the search uses the grid: below, testing all box pairs
+// takes fewer launches.
+constexpr int32_t kGridLoops = 2048;
+
+int64_t grid_buckets(int32_t n_loops) {
+  int64_t b = 64;  // a power of two of at least 4 buckets per loop, at most 2^31
+  while (b < 4 * (int64_t)n_loops && b < ((int64_t)1 << 31)) b *= 2;
+  return b;
+}
+
+lk_status ensure_rows(lk_ctx* ctx, int32_t n_loops) {
+  const size_t L = (size_t)n_loops;
+  lk_status st;
+  if ((st = ensure(ctx, ctx->boxes, 48 * L)) != LK_OK) return st;
+  return ensure(ctx, ctx->pls_rows, 8 * (L / lk::kRowTile + 1) + 4 * L * (1 + lk::kRowSlots));
+}
+
+lk::RowBufs row_bufs(lk_ctx* ctx, int32_t n_loops) {
+  const size_t L = (size_t)n_loops;
+  lk::RowBufs b;
+  b.tiles = (unsigned long long*)ctx->pls_rows.p;
+  b.counts = (int32_t*)((char*)ctx->pls_rows.p + 8 * (L / lk::kRowTile + 1));
+  b.slots = b.counts + L;
+  return b;
+}
+
+// params (64 B) | n_over, n_binned (64) | partials | boxes by place [L][6] f64 |
+// buckets [m] uint2 | bucket counts [m] u32 | bucket of a box, ids by place,
+// boxes tested against all [L] i32 each
+size_t grid_bytes(int32_t n_loops) {
+  return 128 + 8 * 6 * (size_t)lk::kGridStatBlocks + 12 * (size_t)grid_buckets(n_loops) +
+         60 * (size_t)n_loops;
+}
+
+lk::GridBufs grid_bufs(lk_ctx* ctx, int32_t n_loops) {
+  const size_t L = (size_t)n_loops;
+  char* p = (char*)ctx->pls_grid.p;
+  lk::GridBufs g;
+  g.buckets = grid_buckets(n_loops);
+  g.rows.params = (lk::GridParams*)p;
+  g.rows.n_over = (int32_t*)(p + 64);
+  g.n_binned = (uint32_t*)(p + 68);
+  g.part = (double*)(p + 128);
+  g.rows.cell_box = g.part + 6 * lk::kGridStatBlocks;
+  g.rows.cell = (uint2*)(g.rows.cell_box + 6 * L);
+  g.cell_count = (uint32_t*)(g.rows.cell + g.buckets);
+  g.rows.cell_of = (int32_t*)(g.cell_count + g.buckets);
+  g.rows.cell_items = g.rows.cell_of + L;
+  g.rows.over = g.rows.cell_items + L;
+  return g;
+}
+
 bool check_dtype(int d) { return d == LK_F32 || d == LK_F64; }
 
 lk_status set_device(lk_ctx* ctx) {
@@ -767,6 +824,11 @@ lk_status lk_create(lk_ctx** out, int device) {
     delete ctx;
     return LK_EDEVICE;
   }
+  if (hipHostMalloc((void**)&ctx->host_total, 64, hipHostMallocDefault) != hipSuccess) {
+    (void)hipEventDestroy(ctx->done);
+    delete ctx;
+    return LK_ENOMEM;
+  }
   // the no-allocation entry point's device address of `scratch` on this
   // device (a failure is reported by that entry point, not here)
   scratch_setup(device);
@@ -789,7 +851,7 @@ void lk_destroy(lk_ctx* ctx) {
                     &ctx->big_prefix, &ctx->meta,    &ctx->acc,     &ctx->flags,
                     &ctx->refit_list, &ctx->boxes,   &ctx->vcounts, &ctx->vprefix,
                     &ctx->cc_blk,     &ctx->cc_sup,  &ctx->bh_nodes, &ctx->bh_lists,
-                    &ctx->bh_counts,  &ctx->bh_adapt, &ctx->pls_grid, &ctx->dz_piece[0], &ctx->dz_piece[1], &ctx->dz_list[0],
+                    &ctx->bh_counts,  &ctx->bh_adapt, &ctx->pls_grid, &ctx->pls_rows, &ctx->dz_piece[0], &ctx->dz_piece[1], &ctx->dz_list[0],
                     &ctx->dz_list[1], &ctx->dz_pbox, &ctx->dz_gbox, &ctx->dz_mark,
                     &ctx->dz_pre,     &ctx->dz_pair_pre, &ctx->dz_pair_ab, &ctx->dz_part,
                     &ctx->dz_loops};
@@ -798,6 +860,7 @@ void lk_destroy(lk_ctx* ctx) {
   for (auto& e : ctx->ring)
     if (e) hipEventDestroy(e);
   if (ctx->done) hipEventDestroy(ctx->done);
+  if (ctx->host_total) hipHostFree(ctx->host_total);
   delete ctx;
 }
 
@@ -1200,56 +1263,22 @@ lk_status lk_build_pairs(lk_ctx* ctx, const void* xyz, int dtype, const int64_t*
   lk_status st = set_device(ctx);
   if (st != LK_OK) return st;
   hipStream_t s = (hipStream_t)stream;
-  if ((st = ensure(ctx, ctx->boxes, 48 * (size_t)n_loops)) != LK_OK) return st;
-  if ((st = ensure(ctx, ctx->vcounts, 8 * (size_t)n_loops)) != LK_OK) return st;
-  if ((st = ensure(ctx, ctx->vprefix, 8 * (size_t)(n_loops + 1))) != LK_OK) return st;
+  if ((st = ensure_rows(ctx, n_loops)) != LK_OK) return st;
   double* boxes = (double*)ctx->boxes.p;
-  int64_t* cnt = (int64_t*)ctx->vcounts.p;
-  int64_t* pre = (int64_t*)ctx->vprefix.p;
-  // the grid pays off beyond a few thousand loops; both give the same pairs
-  const bool grid = ctx->pair_search == 2 || (ctx->pair_search == 0 && n_loops >= 2048);
+  const lk::RowBufs B = row_bufs(ctx, n_loops);
+  const bool grid = ctx->pair_search == 2 || (ctx->pair_search == 0 && n_loops >= kGridLoops);
   lk::GridBufs G{};
   if (grid) {
-    const size_t L = (size_t)n_loops;
-    G.buckets = 64;  // a power of two of at least 4 buckets per loop
-    while (G.buckets < 4 * (int64_t)n_loops) G.buckets *= 2;
-    const size_t mc = (size_t)G.buckets;
-    const size_t o_cnt = 64, o_start = o_cnt + 8 * mc, o_of = o_start + 8 * (mc + 1);
-    const size_t o_cbox = o_of + 8 * L, o_items = o_cbox + 48 * L;
-    const size_t o_over = o_items + 4 * L, o_nover = o_over + 4 * L;
-    const size_t o_part = o_nover + 64, o_tiles = o_part + 8 * 6 * lk::kGridStatBlocks;
-    const size_t n_tiles = (mc + 4095) / 4096;
-    if ((st = ensure(ctx, ctx->pls_grid, o_tiles + 8 * 2 * (n_tiles + 2))) != LK_OK) return st;
-    char* gb = (char*)ctx->pls_grid.p;
-    G.params = (lk::GridParams*)gb;
-    G.cell_count = (unsigned long long*)(gb + o_cnt);
-    G.cell_start = (int64_t*)(gb + o_start);
-    G.cell_of = (int64_t*)(gb + o_of);
-    G.cell_items = (int32_t*)(gb + o_items);
-    G.cell_box = (double*)(gb + o_cbox);
-    G.over = (int32_t*)(gb + o_over);
-    G.n_over = (int32_t*)(gb + o_nover);
-    G.part = (double*)(gb + o_part);
-    G.tiles = (int64_t*)(gb + o_tiles);
-    G.row_counts = cnt;
+    if ((st = ensure(ctx, ctx->pls_grid, grid_bytes(n_loops))) != LK_OK) return st;
+    G = grid_bufs(ctx, n_loops);
   }
-  LK_HIP(lk::launch_boxes(xyz, dtype == LK_F64, off, n_loops, boxes, s));
-  if (grid)
-    LK_HIP(lk::launch_grid_pairs(boxes, n_loops, G, 0, nullptr, nullptr, s));
-  else
-    LK_HIP(lk::launch_pair_count(boxes, n_loops, cnt, s));
-  LK_HIP(lk::launch_scan(cnt, n_loops, pre, s));
-  int64_t total = 0;
-  LK_HIP(hipMemcpyAsync(&total, pre + n_loops, 8, hipMemcpyDeviceToHost, s));
+  LK_HIP(lk::launch_boxes(xyz, dtype == LK_F64, off, n_loops, boxes, B.tiles, s));
+  if (grid) LK_HIP(lk::launch_grid(boxes, n_loops, G, s));
+  LK_HIP(lk::launch_pair_rows(boxes, n_loops, grid ? &G.rows : nullptr, B, pairs_out, capacity,
+                              ctx->host_total, s));
   LK_HIP(hipStreamSynchronize(s));
+  const int64_t total = *(volatile int64_t*)ctx->host_total;
   *n_pairs = total;
-  if (total > 0 && total <= capacity) {
-    if (grid)
-      LK_HIP(lk::launch_grid_pairs(boxes, n_loops, G, 1, pre, pairs_out, s));
-    else
-      LK_HIP(lk::launch_pair_fill(boxes, n_loops, pre, pairs_out, capacity, s));
-    LK_HIP(hipStreamSynchronize(s));
-  }
   if (total > capacity)
     return ctx->fail(LK_ECAPACITY, "%lld pairs do not fit capacity %lld", (long long)total,
                      (long long)capacity);
@@ -1465,8 +1494,11 @@ lk_status lk_reserve(lk_ctx* ctx, int32_t max_loops, int64_t max_pairs, int64_t 
   if (st != LK_OK) return st;
   if ((st = ensure_workspace(ctx, max_loops, max_pairs)) != LK_OK) return st;
   if ((st = ensure(ctx, ctx->flags, 4 * (size_t)max_pairs)) != LK_OK) return st;
-  if ((st = ensure(ctx, ctx->boxes, 48 * (size_t)max_loops)) != LK_OK) return st;
-  const int64_t nv = max_verify > max_loops ? max_verify : max_loops;
+  if ((st = ensure_rows(ctx, max_loops)) != LK_OK) return st;
+  if (max_loops >= kGridLoops &&
+      (st = ensure(ctx, ctx->pls_grid, grid_bytes(max_loops))) != LK_OK)
+    return st;
+  const int64_t nv = max_verify > 0 ? max_verify : 1;
   if ((st = ensure(ctx, ctx->vcounts, 8 * (size_t)nv)) != LK_OK) return st;
   if ((st = ensure(ctx, ctx->vprefix, 8 * (size_t)(nv + 1))) != LK_OK) return st;
   return LK_OK;
@@ -1677,7 +1709,7 @@ int64_t ctx_workspace_bytes(const lk_ctx* ctx) {
                           &ctx->big_prefix, &ctx->meta,    &ctx->acc,      &ctx->flags,
                           &ctx->refit_list, &ctx->boxes,   &ctx->vcounts,  &ctx->vprefix,
                           &ctx->cc_blk,     &ctx->cc_sup,  &ctx->bh_nodes, &ctx->bh_lists,
-                          &ctx->bh_counts,  &ctx->bh_adapt, &ctx->pls_grid};
+                          &ctx->bh_counts,  &ctx->bh_adapt, &ctx->pls_grid, &ctx->pls_rows};
   int64_t b = 0;
   for (const DevBuf* d : bufs) b += (int64_t)d->bytes;
   return b;
@@ -1689,8 +1721,9 @@ int64_t ctx_workspace_need(int mode, int32_t n_loops, int64_t n_pairs, int64_t n
   // the direct sum's own arrays (ensure_workspace) and its flags
   double b = 12.0 * L + 8.0 * (kPrepMaxBlocks + 1) + 3.0 * sizeof(WorkRec) * P + 8.0 * (P + 1) +
              (double)kMetaBytes + 16.0 * P + 8.0 * P + 4.0 * P;
-  // the pair search: boxes, counts, prefix, and the grid (buckets <= 8 L)
-  b += 48.0 * L + 8.0 * L + 8.0 * (L + 1) + (n_loops >= 2048 ? 192.0 * L + 4096.0 : 0.0);
+  // the pair search: boxes, rows, and the grid
+  b += 48.0 * L + 4.0 * L * (1 + kRowSlots) + 8.0 * (L / kRowTile + 1) +
+       (n_loops >= kGridLoops ? (double)grid_bytes(n_loops) : 0.0);
   // verification's flags and prefix over current + expected pairs
   b += 16.0 * (double)(n_verify + 1);
   if (mode == LK_CROSSINGS)
