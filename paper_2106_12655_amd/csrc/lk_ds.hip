@@ -560,10 +560,11 @@ __device__ __forceinline__ void make_segs(const V3<Tc>* k, Segs<Tc, R>& sg) {
 // roots a step of R = 4 before the arctangents.  The chainmail workload's
 // kernel went from 428 to 320 us, the long loops' from 33.7 to 19.0 ms (73 to
 // 123 TFLOP/s at 90 FLOP a term).
-template <typename Tc, int AT, int R>
-__device__ __forceinline__ void walk_tile(const Vtx<Tc>* l, const Vtx<Tc>* le, bool first,
-                                          const Segs<Tc, R>& sg, double& acc) {
-  // four steps are summed in the compute type before the FP64 lane sum
+// `sink` takes the sums of four steps in the compute type, then those of the
+// last steps one by one; added up in that order in FP64 they are the lane's sum.
+template <typename Tc, int AT, int R, typename Sink>
+__device__ __forceinline__ void walk(const Vtx<Tc>* l, const Vtx<Tc>* le, bool first,
+                                     const Segs<Tc, R>& sg, const Sink& sink) {
   if (l + 4 <= le) {
     Walk<Tc, R> wk;
     walk_init(wk, V3<Tc>{l[0].x, l[0].y, l[0].z}, sg, first);
@@ -579,7 +580,7 @@ __device__ __forceinline__ void walk_tile(const Vtx<Tc>* l, const Vtx<Tc>* le, b
         walk_xy(wk, v1, sg, X, Y);
         s4 += step_angles<Tc, AT, R>(X, Y);
       }
-      acc += (double)s4;
+      sink(s4);
     }
   }
   if (l < le) {
@@ -589,9 +590,15 @@ __device__ __forceinline__ void walk_tile(const Vtx<Tc>* l, const Vtx<Tc>* le, b
       ++l;
       Tc X[R], Y[R];
       walk_xy(wk, V3<Tc>{l[0].x, l[0].y, l[0].z}, sg, X, Y);
-      acc += (double)step_angles<Tc, AT, R>(X, Y);
+      sink(step_angles<Tc, AT, R>(X, Y));
     } while (l < le);
   }
+}
+
+template <typename Tc, int AT, int R>
+__device__ __forceinline__ void walk_tile(const Vtx<Tc>* l, const Vtx<Tc>* le, bool first,
+                                          const Segs<Tc, R>& sg, double& acc) {
+  walk<Tc, AT, R>(l, le, first, sg, [&](Tc sum) { acc += (double)sum; });
 }
 
 // ---------------------------------------------------------------------------
@@ -874,9 +881,8 @@ constexpr int waves_per_simd() {
 
 // Every variant must fit in 256 registers per lane (two waves per SIMD); a
 // test checks the compiled register counts.
-// PK: R small pairs whose loop B fits one wave's lanes share a wave (the
-// throughput layout); without it every small pair gets a whole wave of its
-// own, which shortens each lane's walk (the layout for calls with few pairs).
+// R small pairs whose loop B fits one wave's lanes share a wave (PK, in every
+// variant).
 template <typename Tin, typename Tc, int AT, int R, bool PK = true>
 __global__ __launch_bounds__(kWave, (waves_per_simd<Tc, AT, R>())) void ds_persistent(DsArgs A) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -1039,6 +1045,171 @@ __global__ __launch_bounds__(kWave, (waves_per_simd<Tc, AT, R>())) void ds_persi
   }
 }
 
+// The direct sum of a call with few pairs: one item per workgroup of kTeam waves
+// (a team).  With an item per wave such a call leaves most of the chip idle, or
+// waits for the longest items: an item's walk is up to 4,096 steps long.  A team
+// takes an item's tile in pieces of U steps, a wave each.  The lane sums keep
+// their order to the last bit: a piece's sums of four steps go to LDS in the
+// compute type, and the first wave adds them up in FP64 in the order of the walk
+// while the others stage the next tile.  The pieces start every U steps (a
+// multiple of four) from where the lane's walk of the tile starts, so the groups
+// of four are those of ds_persistent, and a big pair's value is the same in both.
+// A small pair is summed by the team's first wave, all 64 lanes (each walks less
+// of loop A than in a packed round).  ALU-bound as ds_persistent is.
+// Eight waves (FP64: four, which its registers let a compute unit hold two teams
+// of) and U = 64 share the default tile; the LDS of two teams is 2 x 47 KB.
+// Against an item per wave, us per call on one MI355X: 276 pairs of 5 to 5,000
+// segments 1,610 -> 546, neighbours of 100 yarns of up to 16,384 segments 3,330 ->
+// 2,460, of 60 yarns in FP64 3,930 -> 2,560, three pairs of 90,000 segments 21,290
+// -> 21,000 (such pairs fill the chip with items by themselves).  FP32 teams of
+// four waves took 659 and 2,620 us, FP64 teams of eight 2,730.
+template <typename Tc>
+constexpr int kTeam = sizeof(Tc) == 4 ? 8 : 4;
+template <typename Tc>
+constexpr int team_piece(int tile) {
+  const int u = (tile / kTeam<Tc>) & ~3;
+  return u < 4 ? 4 : (u > 64 ? 64 : u);
+}
+template <typename Tc>
+constexpr int team_slots(int tile) { return team_piece<Tc>(tile) / 4 + 3; }
+
+template <typename Tin, typename Tc, int R>
+__global__ __launch_bounds__(kWave * kTeam<Tc>, (sizeof(Tc) == 4 ? 4 : 2)) void ds_team(DsArgs A) {
+  constexpr int AT = sizeof(Tc) == 4 ? 2 : 0;
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  __shared__ unsigned long long next_w;
+  __shared__ int next_stop;
+  Vtx<Tc>* lds = reinterpret_cast<Vtx<Tc>*>(lds_raw);
+  const int n_vtx = A.tile + 2 > kSmallA + 1 ? A.tile + 2 : kSmallA + 1;
+  Tc* slots = reinterpret_cast<Tc*>(lds + n_vtx);
+  const int U = uniform((int32_t)team_piece<Tc>(A.tile)), E = U / 4 + 3;
+  const int wv = uniform((int32_t)(threadIdx.x >> 6));
+  // The thread's index, read again wherever it is used: what comes from it,
+  // kept across the walk, would cost FP32 registers that it has not got.
+  const auto tid = [] {
+    int t = threadIdx.x;
+    if constexpr (sizeof(Tc) == 4) asm volatile("" : "+v"(t));
+    return t;
+  };
+  const Tin* X = static_cast<const Tin*>(A.xyz);
+  const int64_t big_total = uniform(*A.s.big_total);
+  const int64_t n_big = uniform(A.s.counts[1]);
+  const int64_t total = big_total + uniform(A.s.counts[0]);  // small pairs one by one
+
+  // work indices as in ds_persistent, one ahead, in the first thread
+  int64_t w = blockIdx.x;
+  int stop = 0;
+  if (A.out.stop) {
+    if (tid() == 0)
+      next_stop = __hip_atomic_load(A.out.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    stop = uniform(next_stop);
+    __syncthreads();
+  }
+  while (w < total && !stop) {  // the same in every thread
+    unsigned long long wn = 0ull;
+    int sn = 0;
+    if (tid() == 0) {
+      wn = gridDim.x + atomicAdd(A.s.counter, 1ull);
+      if (A.out.stop)
+        sn = __hip_atomic_load(A.out.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (w < big_total) {
+      int64_t lo = 0, hi = n_big;
+      while (hi - lo > 1) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (uniform(A.s.big_prefix[mid]) <= w)
+          lo = mid;
+        else
+          hi = mid;
+      }
+      const WorkRec r = uniform(A.s.big[lo]);
+      const uint32_t fpre = r.items == 1 ? A.out.flags[r.p] : 0u;
+      const int lane = tid() & 63;
+      const int64_t local = w - uniform(A.s.big_prefix[lo]);
+      const Layout L = layout<R>(r, local, A.chunk, lane);
+      Frame<Tin, Tc> F;
+      F.set(X, r.ob + L.b0);
+      F.to_scalar();
+      V3<Tc> kv[R + 1];
+      load_b<Tin, Tc, R>(X, r, L, F, kv);
+      Segs<Tc, R> sg;
+      make_segs<Tc, R>(kv, sg);
+      double acc = 0.0;  // the first wave's
+      for (int t0 = 0; t0 < L.nah; t0 += A.tile) {
+        const int tl = (L.nah - t0) < A.tile ? (L.nah - t0) : A.tile;
+        for (int v = tid(); v <= tl; v += kWave * kTeam<Tc>) {
+          unsigned idx = (unsigned)L.a0 + (unsigned)t0 + (unsigned)v;
+          if (idx >= (unsigned)r.na) idx -= (unsigned)r.na;  // closing vertex of the loop
+          const V3<Tc> x = F.load(X, r.oa + idx);
+          lds[v] = Vtx<Tc>{x.x, x.y, x.z, (Tc)0};
+        }
+        __syncthreads();  // the tile is there, and the slots are read
+        for (int u0 = 0; u0 * U < tl; u0 += kTeam<Tc>) {
+          if (u0 > 0) __syncthreads();  // the slots are read
+          const int ln = tid() & 63;
+          const Layout M = layout<R>(r, local, A.chunk, ln);
+          const int jlo = M.js > t0 ? M.js : t0;
+          const int jhi = M.je < t0 + tl ? M.je : t0 + tl;
+          const int n = M.active && jlo < jhi ? jhi - jlo : 0;  // the lane's steps in this tile
+          const int b = (u0 + wv) * U;
+          const int m = n - b < U ? n - b : U;
+          if (m > 0) {
+            const Vtx<Tc>* l = lds + (jlo - t0 + b);
+            Tc* to = slots + (wv * E) * kWave + ln;
+            walk<Tc, AT, R>(l, l + m, jlo + b == M.js, sg, [&](Tc sum) {
+              *to = sum;
+              to += kWave;
+            });
+          }
+          __syncthreads();
+          if (wv == 0) {
+#pragma unroll 1
+            for (int q = 0; q < kTeam<Tc>; ++q) {
+              const int c = n - (u0 + q) * U < U ? n - (u0 + q) * U : U;
+              const int k = c > 0 ? (c >> 2) + (c & 3) : 0;
+              const Tc* from = slots + (q * E) * kWave + ln;
+#pragma unroll 4
+              for (int e = 0; e < k; ++e) acc += (double)from[e * kWave];
+            }
+          }
+        }
+      }
+      if (wv == 0) finish_item<AT>(acc, r.p, lane, A, r.items == 1, fpre);
+    } else if (wv == 0) {
+      // one small pair on the first wave (one wave: LDS accesses stay in order)
+      const int lane = tid() & 63;
+      const WorkRec cur = uniform(A.s.small[w - big_total]);
+      const uint32_t fm = A.out.flags[cur.p];
+      const Layout L = layout<R>(cur, 0, A.chunk, lane);
+      Frame<Tin, Tc> F;
+      F.set(X, cur.ob);
+      F.to_scalar();
+      V3<Tc> kv[R + 1];
+      load_b<Tin, Tc, R>(X, cur, L, F, kv);
+      const V3<Tc> a_lo = F.load(X, cur.oa + (lane < cur.na ? lane : 0));
+      const V3<Tc> a_hi = F.load(X, cur.oa + (lane + kWave < cur.na ? lane + kWave : 0));
+      if (lane <= cur.na) lds[lane] = Vtx<Tc>{a_lo.x, a_lo.y, a_lo.z, (Tc)0};
+      if (lane + kWave <= cur.na) lds[lane + kWave] = Vtx<Tc>{a_hi.x, a_hi.y, a_hi.z, (Tc)0};
+      Segs<Tc, R> sg;
+      make_segs<Tc, R>(kv, sg);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      double acc = 0.0;
+      if (L.active && L.js < L.je)
+        walk_tile<Tc, AT, R>(lds + L.js, lds + L.je, true, sg, acc);
+      finish_item<AT>(acc, cur.p, lane, A, true, fm);
+    }
+    if (tid() == 0) {
+      next_w = wn;
+      next_stop = sn;
+    }
+    __syncthreads();
+    w = uniform((int64_t)next_w);
+    stop = uniform(next_stop);
+    __syncthreads();
+  }
+}
+
 // Leaf pairs of the Barnes-Hut traversal (Alg. 6, both nodes leaves): Eq. 4
 // over their kBhLeaf x kBhLeaf segment pairs with the walk above.  Like the
 // packed small pairs of the direct sum, a wave takes four leaf pairs at a
@@ -1148,62 +1319,83 @@ size_t lds_bytes(int tile) {
   return (size_t)(n + 1) * sizeof(Vtx<Tc>);
 }
 
-template <typename Tin, typename Tc, int AT, int R, bool PK>
+template <typename Tin, typename Tc, int AT, int R>
 hipError_t launch_t(const DsArgs& a, int grid, hipStream_t s) {
-  const size_t shm = lds_bytes<Tc, R>(a.tile);
-  if constexpr (PK)
-    ds_persistent<Tin, Tc, AT, R><<<dim3(grid), dim3(kWave), shm, s>>>(a);
-  else
-    ds_persistent<Tin, Tc, AT, R, false><<<dim3(grid), dim3(kWave), shm, s>>>(a);
+  ds_persistent<Tin, Tc, AT, R><<<dim3(grid), dim3(kWave), lds_bytes<Tc, R>(a.tile), s>>>(a);
   return hipGetLastError();
 }
 
-template <typename Tin, typename Tc, int AT, int R, bool PK>
+// Workgroups of a kernel that are resident at once, at most `waves_per_cu` waves
+// per compute unit (0: no limit).
+int resident(hipError_t e, int per_cu, int waves, int n_cu, int waves_per_cu) {
+  if (e != hipSuccess || per_cu < 1) per_cu = 1;
+  if (waves_per_cu > 0 && waves_per_cu < per_cu * waves)
+    per_cu = waves_per_cu >= waves ? waves_per_cu / waves : 1;
+  return per_cu * n_cu;
+}
+
+template <typename Tin, typename Tc, int AT, int R>
 int grid_t(int tile, int n_cu, int waves_per_cu) {
   int per_cu = 0;
-  hipError_t e;
-  if constexpr (PK)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, ds_persistent<Tin, Tc, AT, R>, kWave,
-                                                     lds_bytes<Tc, R>(tile));
-  else
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, ds_persistent<Tin, Tc, AT, R, false>,
-                                                     kWave, lds_bytes<Tc, R>(tile));
-  if (e != hipSuccess || per_cu < 1) per_cu = 1;
-  if (waves_per_cu > 0 && waves_per_cu < per_cu) per_cu = waves_per_cu;
-  return per_cu * n_cu;
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+      &per_cu, ds_persistent<Tin, Tc, AT, R>, kWave, lds_bytes<Tc, R>(tile));
+  return resident(e, per_cu, 1, n_cu, waves_per_cu);
+}
+
+// The team kernel's tile, or one small pair's loop A, and the teams' slots.
+template <typename Tc>
+size_t team_lds(int tile) {
+  const int n = tile + 2 > kSmallA + 1 ? tile + 2 : kSmallA + 1;
+  return (size_t)n * sizeof(Vtx<Tc>) + (size_t)kTeam<Tc> * team_slots<Tc>(tile) * kWave * sizeof(Tc);
+}
+template <typename Tin, typename Tc, int R>
+hipError_t launch_team(const DsArgs& a, int grid, hipStream_t s) {
+  ds_team<Tin, Tc, R><<<dim3(grid), dim3(kWave * kTeam<Tc>), team_lds<Tc>(a.tile), s>>>(a);
+  return hipGetLastError();
+}
+template <typename Tin, typename Tc, int R>
+int grid_team(int tile, int n_cu, int waves_per_cu) {
+  int per_cu = 0;
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+      &per_cu, ds_team<Tin, Tc, R>, kWave * kTeam<Tc>, team_lds<Tc>(tile));
+  return resident(e, per_cu, kTeam<Tc>, n_cu, waves_per_cu);
 }
 
 // Kernel variants: input type x arithmetic x arctangent form x segments per lane.
 struct Variant {
   hipError_t (*launch)(const DsArgs&, int, hipStream_t);
   int (*grid)(int, int, int);
+  int waves;  // per workgroup
 };
 
-template <typename Tin, typename Tc, int AT, int R, bool PK = true>
+template <typename Tin, typename Tc, int AT, int R>
 constexpr Variant variant() {
-  return Variant{launch_t<Tin, Tc, AT, R, PK>, grid_t<Tin, Tc, AT, R, PK>};
+  return Variant{launch_t<Tin, Tc, AT, R>, grid_t<Tin, Tc, AT, R>, 1};
+}
+template <typename Tin, typename Tc, int R>
+constexpr Variant team() {
+  return Variant{launch_team<Tin, Tc, R>, grid_team<Tin, Tc, R>, kTeam<Tc>};
 }
 
-// Unpacked layout for calls with few pairs: the direct-sum forms only (the
-// FP32 arctangent forms 0 and 2 give the same values, so both map to 2;
-// with R = 1 nothing is packed anyway).
-bool pick_unpacked(bool in_f64, bool compute_f64, int atan_form, int segs, Variant* v) {
+// The team kernel, for calls with few pairs: the direct-sum forms with the own
+// arctangent and R > 1 only.
+bool pick_team(bool in_f64, bool compute_f64, int atan_form, int segs, Variant* v) {
   if (atan_form == kCrossings || segs < 2) return false;
   if (compute_f64) {
-    *v = in_f64 ? variant<double, double, 0, 2, false>() : variant<float, double, 0, 2, false>();
+    *v = in_f64 ? team<double, double, 2>() : team<float, double, 2>();
     return true;
   }
   if (atan_form == 1) return false;
   if (segs >= 4)
-    *v = in_f64 ? variant<double, float, 2, 4, false>() : variant<float, float, 2, 4, false>();
+    *v = in_f64 ? team<double, float, 4>() : team<float, float, 4>();
   else
-    *v = in_f64 ? variant<double, float, 2, 2, false>() : variant<float, float, 2, 2, false>();
+    *v = in_f64 ? team<double, float, 2>() : team<float, float, 2>();
   return true;
 }
 
 Variant pick(bool in_f64, bool compute_f64, int atan_form, int segs, bool unpacked = false) {
   Variant u;
-  if (unpacked && pick_unpacked(in_f64, compute_f64, atan_form, segs, &u)) return u;
+  if (unpacked && pick_team(in_f64, compute_f64, atan_form, segs, &u)) return u;
   if (compute_f64 && atan_form == kCrossings) {
     constexpr int C = kCrossings;
     if (segs >= 2) return in_f64 ? variant<double, double, C, 2>() : variant<float, double, C, 2>();
@@ -1255,6 +1447,10 @@ hipError_t launch_direct_sum(const DsArgs& a, bool in_f64, bool compute_f64, int
 int direct_sum_grid(bool in_f64, bool compute_f64, int atan_form, int segs, int tile, int n_cu,
                     int waves_per_cu, bool unpacked) {
   return pick(in_f64, compute_f64, atan_form, segs, unpacked).grid(tile, n_cu, waves_per_cu);
+}
+
+int direct_sum_waves(bool in_f64, bool compute_f64, int atan_form, int segs, bool unpacked) {
+  return pick(in_f64, compute_f64, atan_form, segs, unpacked).waves;
 }
 
 }  // namespace lk

@@ -178,9 +178,10 @@ struct Plan {
   bool crossings;  // main pass counts crossings
   bool bh;         // main pass is the Barnes-Hut traversal
   int tile, chunk, grid, grid64, grid_refit, atan_form;
+  int waves;         // of the main pass's grid
   int segs, segs64;  // segments of loop B per lane, FP32 and FP64 kernels
   int grid_cc64;     // CROSSINGS: grid of the FP64 crossing count
-  bool unpacked;     // few pairs: every small pair on a whole wave
+  bool unpacked;     // few pairs: an item per team of waves, a small pair per wave
 };
 
 constexpr int kDefaultSegs32 = 4;
@@ -596,12 +597,15 @@ Plan make_plan(lk_ctx* ctx, bool in_f64, int mode, int64_t n_pairs) {
                                ctx->opt_waves, P.unpacked);
   P.grid64 = lk::direct_sum_grid(in_f64, true, 0, P.segs64, mixed ? default_tile(true) : P.tile,
                                  ctx->n_cu, ctx->opt_waves, P.unpacked);
+  P.waves = mixed ? P.grid * lk::direct_sum_waves(in_f64, false, P.atan_form, P.segs, P.unpacked)
+                  : P.grid64 * lk::direct_sum_waves(in_f64, true, 0, P.segs64, P.unpacked);
   // refits of the direct sum are rare: one wave per CU keeps the empty refit
   // pass cheap (4.7 instead of 7.8 us on chainmail).  Barnes-Hut sends every
   // pair whose far-field error estimate stays too large there (hundreds of
   // big pairs on knit with adaptive beta), so its refit pass gets the whole
   // grid.
-  P.grid_refit = P.bh || ctx->n_cu >= P.grid64 ? P.grid64 : ctx->n_cu;
+  const int refit = ctx->n_cu / lk::direct_sum_waves(in_f64, true, 0, P.segs64, P.unpacked);
+  P.grid_refit = P.bh || refit >= P.grid64 ? P.grid64 : refit;
   P.grid_cc64 = P.crossings ? lk::direct_sum_grid(in_f64, true, kFormCrossings, P.segs64,
                                                   default_tile(true), ctx->n_cu, 0)
                             : 0;
@@ -1040,7 +1044,7 @@ lk_status direct_sum_enqueue(lk_ctx* ctx, const void* xyz, int dtype, const int6
 
   ctx->stats.tile_a = P.tile;
   ctx->stats.chunk_a = P.chunk;
-  ctx->stats.waves_per_cu = (mixed ? P.grid : P.grid64) / (ctx->n_cu > 0 ? ctx->n_cu : 1);
+  ctx->stats.waves_per_cu = P.waves / (ctx->n_cu > 0 ? ctx->n_cu : 1);
   ctx->stats.atan_form = P.atan_form;
   ctx->stats.segs_per_lane = mixed ? P.segs : P.segs64;
   ctx->last_stream = s;
@@ -1199,7 +1203,7 @@ lk_status lk_direct_sum_noalloc(lk_ctx* ctx, const void* xyz, int dtype, const i
   const Plan P = make_plan(ctx, dtype == LK_F64, mode, n_pairs);
   ctx->stats.tile_a = P.tile;
   ctx->stats.chunk_a = P.chunk;
-  ctx->stats.waves_per_cu = (mixed ? P.grid : P.grid64) / (ctx->n_cu > 0 ? ctx->n_cu : 1);
+  ctx->stats.waves_per_cu = P.waves / (ctx->n_cu > 0 ? ctx->n_cu : 1);
   ctx->stats.atan_form = P.atan_form;
   ctx->stats.segs_per_lane = mixed ? P.segs : P.segs64;
   // eager launches only: instantiating a graph would allocate
