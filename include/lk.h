@@ -186,7 +186,7 @@ lk_status lk_direct_sum_check(lk_ctx* ctx, const void* xyz, int dtype,
  * capture, tight serving loops, harnesses that forbid hipMalloc.  The same
  * computation and kernels as lk_direct_sum in the PLAIN_F64 and MIXED modes
  * (bitwise equal results for the same context options), with the call's
- * workspace in one static device array of the library (about 17.6 MiB, held
+ * workspace in one static device array of the library (about 17.4 MiB, held
  * by each device the library runs on until the process ends) instead of the
  * context's buffers.  The call allocates nothing: no hipMalloc, hipFree or
  * graph instantiation; the kernels are launched eagerly on `stream` (which a

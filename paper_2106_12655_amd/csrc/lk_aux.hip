@@ -1066,35 +1066,205 @@ __global__ __launch_bounds__(256) void verify_scatter_k(const int32_t* pr, const
   }
 }
 
-// Preparation, plan and schedule of a call with few pairs in one launch of a
-// single workgroup: the per-loop scan of prep_k (16 lanes per loop, so 64
-// loops are scanned at once and their loads overlap), xi as this workgroup's
-// fixed-order sum, then the plan and the schedule.  Each step reads only
-// what the workgroup wrote before a barrier.  Used where the pairs are at
-// most two per compute unit: there three launches cost more than their work
-// (a call with few but very long loops scans them with one workgroup only,
-// which its direct sum dwarfs).
+// Preparation, plan and schedule of a call with few pairs in one launch: the
+// per-loop scan of prep_k, xi in a fixed order, then the plan and the schedule.
+// Small scenes are scanned by the first workgroup (16 lanes per loop, so 64 loops
+// at once and their loads overlap) and the others leave.  Otherwise the vertices
+// are scanned in equal pieces, a wavefront each, whatever the loops' sizes, and
+// the workgroup that ends last puts the pieces together, plans and schedules
+// (each step reads only what was written before a barrier, or before the ticket).
+// A step of 16 lanes takes 0.16 us and the pieces' fences and ticket 12 us, so the
+// line lies at some 64 steps: us per call with one workgroup / in pieces at 64
+// loops of 32 vertices 23.6 / 36.4, 64 of 512 31.0 / 36.5, 1,000 of 8 32.8 / 34.7,
+// 4 of 2,048 41.7 / 36.5, 2 of 8,192 104 / 36.5, 2 of 32,768 364 / 36.4.  Per call
+// of 100 yarns of up to 16,384 vertices this launch went from 331 to 25 us, of
+// three pairs of 90,000 vertices from 2,200 to 25 us.
+constexpr int64_t kPrepAloneVertices = 32768, kPrepAloneLoop = 1024;
+constexpr int32_t kPrepAloneLoops = 1024;
+
+// What the pieces leave.  A loop is owned by the piece that its first vertex is
+// in; one that ends in there is complete and goes to lf and minseg2 directly.
+struct PrepPieces {
+  unsigned* ticket;
+  double *xi, *head_min, *tail_min;     // sums; minima of the parts below
+  uint32_t *head_flags, *tail_flags;
+  int32_t *head_owner;  // the piece's first part, of a loop that another piece owns (-1: none)
+  int32_t *tail_loop;   // the piece's last part, of an own loop that goes on (-1: none)
+  __host__ __device__ explicit PrepPieces(void* p) {
+    char* c = static_cast<char*>(p);
+    ticket = (unsigned*)c;
+    xi = (double*)(c + 256);
+    head_min = xi + kPrepPieces;
+    tail_min = head_min + kPrepPieces;
+    head_flags = (uint32_t*)(tail_min + kPrepPieces);
+    tail_flags = head_flags + kPrepPieces;
+    head_owner = (int32_t*)(tail_flags + kPrepPieces);
+    tail_loop = head_owner + kPrepPieces;
+  }
+};
+
+// The first loop that starts at vertex x or later (off[0] = 0), found by a wavefront.
+__device__ int32_t first_loop_from(const int64_t* off, int32_t L, int64_t x, int lane) {
+  int32_t lo = 0, hi = L;  // starts below lo are before x, those from hi on are not
+  while (lo < hi) {
+    const int32_t step = (hi - lo + 63) / 64;
+    const int64_t at = lo + (int64_t)lane * step;
+    const bool before = at < hi && off[at] - off[0] < x;
+    const int n = __popcll(__ballot(before));  // a prefix of the lanes
+    if (n == 0) return lo;
+    const int64_t top = lo + (int64_t)n * step;
+    lo += (n - 1) * step + 1;
+    hi = top < hi ? (int32_t)top : hi;
+  }
+  return lo;
+}
+
+// Vertices a .. b - 1 of loop l (positions from the loop's first): flags and
+// shortest squared segment in every lane, the lane's sum of coordinates returned.
+template <typename Tin>
+__device__ double scan_part(const Tin* X, const int64_t* off, int32_t l, int64_t a, int64_t b,
+                            int lane, uint32_t* flags, double* shortest) {
+  const int64_t o = off[l], n = off[l + 1] - o;
+  uint32_t f = 0u;
+  double s = 0.0, mn = INFINITY;
+#pragma unroll 4
+  for (int64_t q = a + lane; q < b; q += 64) {
+    const Tin* P = X + 3 * (o + q);
+    const Tin* Q = X + 3 * (o + (q + 1 == n ? 0 : q + 1));
+    const double x0 = (double)P[0], y0 = (double)P[1], z0 = (double)P[2];
+    const double dx = (double)Q[0] - x0, dy = (double)Q[1] - y0, dz = (double)Q[2] - z0;
+    if (!isfinite(x0) || !isfinite(y0) || !isfinite(z0)) f |= kFlagNonfinite | kFlagBadloop;
+    s += fabs(x0) + fabs(y0) + fabs(z0);
+    mn = fmin(mn, dx * dx + dy * dy + dz * dz);
+  }
+  for (int w = 32; w > 0; w >>= 1) {
+    f |= (uint32_t)__shfl_xor((int)f, w);
+    mn = fmin(mn, __shfl_xor(mn, w));
+  }
+  *flags = f;
+  *shortest = mn;
+  return s;
+}
+
+template <typename Tin>
+__device__ void scan_piece(const Tin* X, const int64_t* off, int32_t L, int64_t V, int32_t k,
+                           int lane, uint32_t* lf, double* minseg2, const PrepPieces& P) {
+  const int64_t len = (V + kPrepPieces - 1) / kPrepPieces, o0 = off[0];
+  const int64_t s = k * len, e = s + len < V ? s + len : V;
+  const int32_t l0 = first_loop_from(off, L, s, lane);
+  const int32_t l1 = k == kPrepPieces - 1 ? L : first_loop_from(off, L, s + len, lane);
+  double sum = 0.0, mn = INFINITY;
+  uint32_t f = 0u;
+  const int64_t end0 = off[l0] - o0;  // of the loop before l0
+  const bool head = l0 > 0 && end0 > s;
+  int32_t owner = -1;
+  if (head) {
+    const int64_t o = off[l0 - 1] - o0;
+    owner = (int32_t)(o / len);
+    sum += scan_part(X, off, l0 - 1, s - o, (end0 < e ? end0 : e) - o, lane, &f, &mn);
+  }
+  if (lane == 0) {
+    P.head_owner[k] = owner;
+    P.head_flags[k] = f;
+    P.head_min[k] = mn;
+  }
+  int32_t tail = -1;
+  f = 0u;
+  mn = INFINITY;
+  for (int32_t l = l0; l < l1; ++l) {
+    const int64_t o = off[l] - o0, n = off[l + 1] - off[l];
+    const bool on = o + n > e;  // the last of them
+    sum += scan_part(X, off, l, 0, on ? e - o : n, lane, &f, &mn);
+    if (n < 3) f |= kFlagBadloop;
+    if (on) {
+      tail = l;
+    } else if (lane == 0) {
+      lf[l] = f;
+      minseg2[l] = mn;
+    }
+  }
+  for (int w = 32; w > 0; w >>= 1) sum += __shfl_xor(sum, w);
+  if (lane == 0) {
+    P.tail_loop[k] = tail;
+    P.tail_flags[k] = f;
+    P.tail_min[k] = mn;
+    P.xi[k] = sum;
+  }
+}
+
+// The parts of loops that several pieces scanned, one workgroup; returns the
+// thread's part of the sum of coordinates.
+__device__ double join_pieces(const PrepPieces& P, uint32_t* lf, double* minseg2) {
+  __shared__ unsigned long long mn[kPrepPieces];  // of squares: ordered as their bits
+  __shared__ uint32_t f[kPrepPieces];
+  double s = 0.0;
+  for (int k = threadIdx.x; k < kPrepPieces; k += 1024) {
+    mn[k] = (unsigned long long)__double_as_longlong(P.tail_min[k]);
+    f[k] = P.tail_flags[k];
+    s += P.xi[k];
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < kPrepPieces; k += 1024) {
+    const int32_t o = P.head_owner[k];
+    if (o < 0) continue;
+    atomicMin(&mn[o], (unsigned long long)__double_as_longlong(P.head_min[k]));
+    atomicOr(&f[o], P.head_flags[k]);
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < kPrepPieces; k += 1024) {
+    const int32_t l = P.tail_loop[k];
+    if (l < 0) continue;
+    lf[l] = f[k];
+    minseg2[l] = __longlong_as_double((long long)mn[k]);
+  }
+  return s;
+}
+
 template <typename Tin>
 __global__ __launch_bounds__(1024) void prep_plan_k(const Tin* X, PlanArgs A, int32_t L,
                                                     LoopInfo li, uint32_t* lf, double* minseg2,
-                                                    Sched S, unsigned long long* zero_mismatch,
+                                                    Sched S, PrepPieces P,
+                                                    unsigned long long* zero_mismatch,
                                                     int32_t* zero_stop, int32_t* zero_next) {
   __shared__ double red[1024];
+  __shared__ unsigned order;
+  const int64_t nv = A.off[L] - A.off[0];
+  const int64_t ln = threadIdx.x < L ? A.off[threadIdx.x + 1] - A.off[threadIdx.x] : 0;
+  const bool alone =
+      !__syncthreads_or(ln > kPrepAloneLoop) && nv <= kPrepAloneVertices && L <= kPrepAloneLoops;
+  if (alone && blockIdx.x > 0) return;
+  double s = 0.0;
+  if (!alone) {
+    scan_piece(X, A.off, L, nv, (int32_t)(blockIdx.x * 16 + (threadIdx.x >> 6)),
+               (int)(threadIdx.x & 63), lf, minseg2, P);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      __threadfence();  // the workgroup's pieces before its ticket
+      order = atomicAdd(P.ticket, 1u);
+    }
+    __syncthreads();
+    if (order != gridDim.x - 1) return;
+    __threadfence();  // every workgroup's pieces
+    if (threadIdx.x == 0) *P.ticket = 0u;  // for the next launch
+  }
   if (threadIdx.x < 2) S.counts[threadIdx.x] = 0;
   if (threadIdx.x == 0 && zero_mismatch) {
     *zero_mismatch = 0ull;
     *zero_stop = 0;
   }
-  const int sub = threadIdx.x & 15, group = threadIdx.x >> 4;
-  double s = 0.0;
-  for (int64_t l = group; l < L; l += 64) s += scan_loop<Tin, 16>(X, A.off, l, sub, lf, minseg2);
+  if (alone) {
+    const int sub = threadIdx.x & 15, group = threadIdx.x >> 4;
+    for (int64_t l = group; l < L; l += 64)
+      s += scan_loop<Tin, 16>(X, A.off, l, sub, lf, minseg2);
+  } else {
+    s = join_pieces(P, lf, minseg2);
+  }
   red[threadIdx.x] = s;
   __syncthreads();
   for (int w = 512; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
-  const int64_t nv = A.off[L] - A.off[0];
   const double xi = nv > 0 ? red[0] / (3.0 * (double)nv) : 0.0;
   plan_positions(A, L, li, S, 0, xi, A.n_list, 0, 1024);
   __syncthreads();
@@ -1166,15 +1336,16 @@ hipError_t launch_sched(const Sched& sc, int32_t* zero_next, hipStream_t s) {
 
 hipError_t launch_prep_plan(const void* xyz, bool in_f64, const PlanArgs& a, int32_t n_loops,
                             const LoopInfo& li, uint32_t* lf, double* minseg2, const Sched& sc,
-                            unsigned long long* zero_mismatch, int32_t* zero_stop,
+                            void* pieces, unsigned long long* zero_mismatch, int32_t* zero_stop,
                             int32_t* zero_next, hipStream_t s) {
   if (a.list || a.n_list_dev) return hipErrorInvalidValue;  // the main pass only
+  const PrepPieces pc(pieces);
   if (in_f64)
-    prep_plan_k<double><<<1, 1024, 0, s>>>((const double*)xyz, a, n_loops, li, lf, minseg2, sc,
-                                          zero_mismatch, zero_stop, zero_next);
+    prep_plan_k<double><<<kPrepGroups, 1024, 0, s>>>((const double*)xyz, a, n_loops, li, lf,
+                                                    minseg2, sc, pc, zero_mismatch, zero_stop, zero_next);
   else
-    prep_plan_k<float><<<1, 1024, 0, s>>>((const float*)xyz, a, n_loops, li, lf, minseg2, sc,
-                                         zero_mismatch, zero_stop, zero_next);
+    prep_plan_k<float><<<kPrepGroups, 1024, 0, s>>>((const float*)xyz, a, n_loops, li, lf,
+                                                   minseg2, sc, pc, zero_mismatch, zero_stop, zero_next);
   return hipGetLastError();
 }
 

@@ -231,6 +231,7 @@ struct Ws {
   uint32_t* loop_flags;     // [L]
   double* minseg2;          // [L]
   double* xi;               // [kPrepMaxBlocks + 1]
+  void* pieces;             // [kPrepPieceBytes], its ticket 0 between calls
   lk::WorkRec* recs;        // [3 P]
   int64_t* big_prefix;      // [P + 1]
   char* meta;               // [kMetaBytes]
@@ -246,7 +247,8 @@ Ws ctx_ws(lk_ctx* ctx) {
   Ws w;
   w.loop_flags = (uint32_t*)ctx->loop_flags.p;
   w.minseg2 = (double*)ctx->minseg2.p;
-  w.xi = (double*)ctx->xi.p;
+  w.pieces = ctx->xi.p;
+  w.xi = (double*)((char*)ctx->xi.p + lk::kPrepPieceBytes);
   w.recs = (lk::WorkRec*)ctx->recs.p;
   w.big_prefix = (int64_t*)ctx->big_prefix.p;
   w.meta = (char*)ctx->meta.p;
@@ -488,8 +490,8 @@ lk_status enqueue_direct_sum(lk_ctx* ctx, const Ws& W, const Plan& P, const void
     LK_HIP(launch_bh_finalize(H, n_pairs, s));
   } else {
     if (one_launch_start) {
-      LK_HIP(launch_prep_plan(xyz, P.in_f64, M, n_loops, li, lf, W.minseg2, A.s, out.n_mismatch,
-                              out.stop, W.at<int32_t>(kMetaCountsRefit), s));
+      LK_HIP(launch_prep_plan(xyz, P.in_f64, M, n_loops, li, lf, W.minseg2, A.s, W.pieces,
+                              out.n_mismatch, out.stop, W.at<int32_t>(kMetaCountsRefit), s));
     } else {
       LK_HIP(launch_plan(M, n_loops, li, A.s, false, s));
       LK_HIP(launch_sched(A.s, W.at<int32_t>(kMetaCountsRefit), s));
@@ -612,18 +614,45 @@ Plan make_plan(lk_ctx* ctx, bool in_f64, int mode, int64_t n_pairs) {
   return P;
 }
 
-lk_status ensure_workspace(lk_ctx* ctx, int32_t n_loops, int64_t n_pairs) {
+// The preparation's partial results.  Their ticket is cleared when they are
+// allocated: on the call's stream, or, where that is being captured (the graph may
+// never be replayed) or there is none, at once on a stream of its own.
+lk_status ensure_partials(lk_ctx* ctx, hipStream_t s, bool have_stream) {
+  if (ctx->xi.p) return LK_OK;
+  lk_status st =
+      ensure(ctx, ctx->xi, lk::kPrepPieceBytes + 8 * (size_t)(lk::kPrepMaxBlocks + 1));
+  if (st != LK_OK) return st;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  hipError_t e = have_stream ? hipStreamIsCapturing(s, &cap) : hipSuccess;
+  if (e == hipSuccess && have_stream && cap == hipStreamCaptureStatusNone) {
+    e = lk::launch_zero_i64((int64_t*)ctx->xi.p, s);
+  } else if (e == hipSuccess) {
+    hipStream_t own = nullptr;
+    e = hipStreamCreateWithFlags(&own, hipStreamNonBlocking);
+    if (e == hipSuccess) {
+      e = lk::launch_zero_i64((int64_t*)ctx->xi.p, own);
+      if (e == hipSuccess) e = hipStreamSynchronize(own);
+      (void)hipStreamDestroy(own);
+    }
+  }
+  if (e == hipSuccess) return LK_OK;
+  (void)hipFree(ctx->xi.p);
+  ctx->xi = DevBuf();
+  return ctx->fail(LK_EDEVICE, "clearing workspace: %s", hipGetErrorString(e));
+}
+
+lk_status ensure_workspace(lk_ctx* ctx, int32_t n_loops, int64_t n_pairs, hipStream_t s,
+                           bool have_stream = true) {
   lk_status st;
   if ((st = ensure(ctx, ctx->loop_flags, 4 * (size_t)n_loops)) != LK_OK) return st;
   if ((st = ensure(ctx, ctx->minseg2, 8 * (size_t)n_loops)) != LK_OK) return st;
-  if ((st = ensure(ctx, ctx->xi, 8 * (size_t)(lk::kPrepMaxBlocks + 1))) != LK_OK) return st;
   if ((st = ensure(ctx, ctx->recs, 3 * sizeof(lk::WorkRec) * (size_t)n_pairs)) != LK_OK) return st;
   if ((st = ensure(ctx, ctx->big_prefix, 8 * (size_t)(n_pairs + 1))) != LK_OK) return st;
   if ((st = ensure(ctx, ctx->meta, kMetaBytes)) != LK_OK) return st;
   if ((st = ensure(ctx, ctx->acc, 16 * (size_t)n_pairs)) != LK_OK) return st;
   // two refit lists: the second is the CROSSINGS mode's FP64 direct-sum pass
   if ((st = ensure(ctx, ctx->refit_list, 8 * (size_t)n_pairs)) != LK_OK) return st;
-  return LK_OK;
+  return ensure_partials(ctx, s, have_stream);
 }
 
 // Crossing count: size the culling boxes for the call's vertex count, which
@@ -691,6 +720,11 @@ int64_t grid_buckets(int32_t n_loops) {
 lk_status ensure_rows(lk_ctx* ctx, int32_t n_loops) {
   const size_t L = (size_t)n_loops;
   lk_status st;
+  if (!ctx->host_total &&
+      hipHostMalloc((void**)&ctx->host_total, 64, hipHostMallocDefault) != hipSuccess) {
+    ctx->host_total = nullptr;
+    return ctx->fail(LK_ENOMEM, "hipHostMalloc failed");
+  }
   if ((st = ensure(ctx, ctx->boxes, 48 * L)) != LK_OK) return st;
   return ensure(ctx, ctx->pls_rows, 8 * (L / lk::kRowTile + 1) + 4 * L * (1 + lk::kRowSlots));
 }
@@ -752,12 +786,13 @@ constexpr size_t al256(size_t b) { return (b + 255) / 256 * 256; }
 // Byte offsets of the workspace arrays for L loops and P pairs (each aligned
 // to 256 bytes; the same arrays and sizes as ensure_workspace, plus flags).
 struct NoallocLayout {
-  size_t lf, minseg2, xi, recs, big_prefix, meta, acc, refit, flags, total;
+  size_t pieces, lf, minseg2, xi, recs, big_prefix, meta, acc, refit, flags, total;
 };
 
 constexpr NoallocLayout noalloc_layout(size_t L, size_t P) {
   NoallocLayout y{};
-  y.lf = 0;
+  y.pieces = 0;  // the same place for every size: its ticket is 0 between calls
+  y.lf = al256(lk::kPrepPieceBytes);
   y.minseg2 = y.lf + al256(4 * L);
   y.xi = y.minseg2 + al256(8 * L);
   y.recs = y.xi + al256(8 * (size_t)(lk::kPrepMaxBlocks + 1));
@@ -775,7 +810,7 @@ constexpr size_t kNoallocBytes =
 
 }  // namespace
 
-// The no-allocation entry point's workspace (about 17.6 MiB; each device the
+// The no-allocation entry point's workspace (about 17.4 MiB; each device the
 // library runs on holds its own copy until the process ends).  Host code
 // never passes this name to a kernel: it stands for a host-side shadow, not
 // the device address, which is looked up per device below.
@@ -827,11 +862,6 @@ lk_status lk_create(lk_ctx** out, int device) {
   if (hipEventCreateWithFlags(&ctx->done, hipEventDisableTiming) != hipSuccess) {
     delete ctx;
     return LK_EDEVICE;
-  }
-  if (hipHostMalloc((void**)&ctx->host_total, 64, hipHostMallocDefault) != hipSuccess) {
-    (void)hipEventDestroy(ctx->done);
-    delete ctx;
-    return LK_ENOMEM;
   }
   // the no-allocation entry point's device address of `scratch` on this
   // device (a failure is reported by that entry point, not here)
@@ -1029,7 +1059,7 @@ lk_status direct_sum_enqueue(lk_ctx* ctx, const void* xyz, int dtype, const int6
   const bool in_f64 = dtype == LK_F64;
   const bool mixed = mode != LK_PLAIN_F64;
   const Plan P = make_plan(ctx, in_f64, mode, n_pairs);
-  if ((st = ensure_workspace(ctx, n_loops, n_pairs)) != LK_OK) return st;
+  if ((st = ensure_workspace(ctx, n_loops, n_pairs, s)) != LK_OK) return st;
   if (P.crossings || P.bh) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (s && hipStreamIsCapturing(s, &cs) != hipSuccess) cs = hipStreamCaptureStatusNone;
@@ -1192,6 +1222,7 @@ lk_status lk_direct_sum_noalloc(lk_ctx* ctx, const void* xyz, int dtype, const i
   W.loop_flags = (uint32_t*)(base + y.lf);
   W.minseg2 = (double*)(base + y.minseg2);
   W.xi = (double*)(base + y.xi);
+  W.pieces = base + y.pieces;
   W.recs = (lk::WorkRec*)(base + y.recs);
   W.big_prefix = (int64_t*)(base + y.big_prefix);
   W.meta = base + y.meta;
@@ -1496,7 +1527,7 @@ lk_status lk_reserve(lk_ctx* ctx, int32_t max_loops, int64_t max_pairs, int64_t 
     return ctx->fail(LK_EINVAL, "bad reservation sizes");
   lk_status st = set_device(ctx);
   if (st != LK_OK) return st;
-  if ((st = ensure_workspace(ctx, max_loops, max_pairs)) != LK_OK) return st;
+  if ((st = ensure_workspace(ctx, max_loops, max_pairs, nullptr, false)) != LK_OK) return st;
   if ((st = ensure(ctx, ctx->flags, 4 * (size_t)max_pairs)) != LK_OK) return st;
   if ((st = ensure_rows(ctx, max_loops)) != LK_OK) return st;
   if (max_loops >= kGridLoops &&
@@ -1585,7 +1616,7 @@ lk_status lk_autotune(lk_ctx* ctx, const void* xyz, int dtype, const int64_t* of
     }
   }
 
-  if ((st = ensure_workspace(ctx, n_loops, n_pairs)) != LK_OK) return st;
+  if ((st = ensure_workspace(ctx, n_loops, n_pairs, s)) != LK_OK) return st;
   if (crossings && (st = cc_prepare(ctx, off, n_loops, s, true)) != LK_OK) return st;
   if (!flags) {
     if ((st = ensure(ctx, ctx->flags, 4 * (size_t)n_pairs)) != LK_OK) return st;
@@ -1723,8 +1754,9 @@ int64_t ctx_workspace_need(int mode, int32_t n_loops, int64_t n_pairs, int64_t n
                            int64_t n_verify) {
   const double L = (double)n_loops, P = (double)n_pairs, V = (double)n_vertices;
   // the direct sum's own arrays (ensure_workspace) and its flags
-  double b = 12.0 * L + 8.0 * (kPrepMaxBlocks + 1) + 3.0 * sizeof(WorkRec) * P + 8.0 * (P + 1) +
-             (double)kMetaBytes + 16.0 * P + 8.0 * P + 4.0 * P;
+  double b = 12.0 * L + 8.0 * (kPrepMaxBlocks + 1) + (double)kPrepPieceBytes +
+             3.0 * sizeof(WorkRec) * P + 8.0 * (P + 1) + (double)kMetaBytes + 16.0 * P +
+             8.0 * P + 4.0 * P;
   // the pair search: boxes, rows, and the grid
   b += 48.0 * L + 4.0 * L * (1 + kRowSlots) + 8.0 * (L / kRowTile + 1) +
        (n_loops >= kGridLoops ? (double)grid_bytes(n_loops) : 0.0);

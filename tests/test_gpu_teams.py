@@ -1,4 +1,4 @@
-"""Calls with few pairs: an item per team of waves.
+"""Calls with few pairs: an item per team of waves, and the preparation in pieces.
 
 Beyond two pairs per compute unit a call runs an item per wave instead.  A big
 pair (loop A of 128 segments or more, or several items) is summed in the same
@@ -69,3 +69,38 @@ def test_teams_sum_in_the_same_order(ctx, mode, dtype, options):
     assert np.array_equal(few[1], np.rint(want))
     if mode == "plain":
         assert np.abs(few[0] - want).max() < 2e-9
+
+
+@pytest.mark.parametrize("sizes", [
+    [1024, 1024], [1025, 1024], [32] * 1024, [32] * 1023 + [33], [7] * 1025,
+    [0, 1, 2, 3, 9000, 0, 0, 5, 40000, 3, 0], [100003, 5], [7] * 3000,
+    [3, 0, 2500, 4, 1] * 40], ids=lambda s: "%d-%d" % (len(s), sum(s)))
+def test_preparation_in_pieces(ctx, sizes):
+    """Flags of loops with a bad vertex or a zero-length segment at the pieces'
+    ends equal those of a call with many pairs, which scans a loop per wave."""
+    import torch
+    xyz, off = _pack(sizes, np.float64, 5)
+    n = len(xyz)
+    piece = -(-n // 2048)
+    rng = np.random.default_rng(len(sizes))
+    x = torch.from_numpy(xyz).cuda()
+    o = torch.from_numpy(off).cuda()
+    loops = np.arange(len(sizes))
+    # each of the chosen loops in a pair with the first (both orders of the index)
+    chosen = rng.choice(loops, min(len(loops), 250), replace=False)
+    pairs = [(int(a), int((a + 1) % max(2, len(loops)))) for a in chosen]
+    print(len(sizes), "loops", n, "vertices", flush=True)
+    for plant in range(6):
+        y = x.clone()
+        at = {0: [], 1: [piece * (n // piece // 2)], 2: [piece * 3 - 1, n - 1],
+              3: [0], 4: [piece * k for k in range(1, n // piece, 97)], 5: [n // 2, n // 3]}[plant]
+        for v in at:
+            if plant % 2:
+                y[v] = float("nan") if plant == 1 else float("inf")
+            else:  # repeats the vertex before it in its loop: no length
+                l = int(np.searchsorted(off, v, "right")) - 1
+                y[v] = y[v - 1 if v > off[l] else off[l + 1] - 1]
+        few = _run(ctx, y, o, pairs, "mixed")
+        many = [t[:len(pairs)] for t in _run(ctx, y, o, pairs * (1 + 600 // len(pairs)), "mixed")]
+        assert np.array_equal(few[2] & ~1, many[2] & ~1), plant
+        assert np.array_equal(few[1], many[1]), plant
