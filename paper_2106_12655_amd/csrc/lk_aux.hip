@@ -343,9 +343,9 @@ __device__ void schedule(const Sched& S, int32_t* zero_next) {
   }
   __syncthreads();
   const int64_t total = block_scan_array(S.big_prefix, nb, S.big_prefix, wsum);
+  if (t < kQueues) S.counter[t * kQueueStride] = 0ull;
   if (t == 0) {
     *S.big_total = total;
-    *S.counter = 0ull;
     if (zero_next) {
       zero_next[0] = 0;
       zero_next[1] = 0;

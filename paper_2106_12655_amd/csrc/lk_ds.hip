@@ -12,8 +12,8 @@
 //   * when loop B has fewer than 64 segments left, the lanes split loop A's
 //     range into groups instead (both loops parallel, as the paper does for
 //     small pairs).
-// The kernel is persistent: a fixed grid of waves pulls items from a device
-// counter until the device-side item total is reached, so the launch shape
+// The kernel is persistent: a fixed grid of waves pulls items from device
+// counters until the device-side item total is reached, so the launch shape
 // does not depend on the data and the whole pass can live in a HIP graph.
 //
 // Per term (Eq. 4, Sec. 2.1): a = l_j - k_i, b = l_j - k_{i+1},
@@ -746,8 +746,13 @@ __device__ __forceinline__ void walk_tile(const Vtx<Tc>* l, const Vtx<Tc>* le, b
   cc_init(wk, V3<Tc>{l[0].x, l[0].y, l[0].z}, sg);
   int cnt = 0;
   bool bad = false;
+  V3<Tc> next{l[1].x, l[1].y, l[1].z};  // read a step ahead
 #pragma unroll 2
-  for (; l < le; ++l) cc_step(wk, V3<Tc>{l[1].x, l[1].y, l[1].z}, sg, cnt, bad);
+  for (; l < le; ++l) {
+    const V3<Tc> l1 = next;
+    next = {l[2].x, l[2].y, l[2].z};
+    cc_step(wk, l1, sg, cnt, bad);
+  }
   acc += bad ? __builtin_nan("") : (double)cnt;
 }
 
@@ -861,7 +866,7 @@ __device__ __forceinline__ void finish_item(double acc, int32_t p, int lane, con
 // While transcendentals left the waves out of step (sqrt_n), the placement moved
 // a call's time by 7-10%; now offsets of 0-16 bytes give 349.3-350.4 us on the
 // chainmail workload.  A CPU test checks the placements.
-constexpr int kPadPacked = 2, kPadWhole = 1, kPadBig = 1;
+constexpr int kPadPacked = 3, kPadWhole = 1, kPadBig = 1;
 template <typename Tin, typename Tc, int AT, int R, bool PK, int N>
 __device__ __forceinline__ void place_code() {
   if constexpr (PK && sizeof(Tin) == 4 && sizeof(Tc) == 4 && AT == 2 && R == 4 && N > 0)
@@ -895,11 +900,23 @@ __global__ __launch_bounds__(kWave, (waves_per_simd<Tc, AT, R>())) void ds_persi
   const int64_t total = big_total + (n_small + A.batch - 1) / A.batch;
 
   // A wave's first work index is its workgroup index, so a launch with fewer
-  // items than waves costs no atomic at all; later indices come from the
-  // device counter, offset by the grid.  The next index is fetched one item
-  // ahead so the atomic's latency overlaps the current item's arithmetic; a
-  // fused check's stop flag is read with it (device-scope load, so another
-  // wave's store is seen).
+  // items than waves costs no atomic at all; later indices, offset by the grid,
+  // come from a device counter.  An atomic on one counter takes 5 ns, so many
+  // short items get kQueues of them: queue q hands out the indices that are q
+  // modulo the number of queues, to the waves whose index is.  Split pairs' items
+  // are long and differ, and their list starts with the largest: below eight per
+  // wave they stay in one queue.  With one queue / 16, us per call on one MI355X:
+  // 69,041 pairs of 64 x 64 segments, mixed 347 / 283, crossings 294 / 186; 13,000
+  // of 61 x 61 in FP64 267 / 248; 20,000 of 128 x 3 366 / 167, of 150 x 150 808 /
+  // 730; 700 pairs of 1,500 x 1,500 in FP64 (8,400 items) 4,085 / 4,210.
+  // The next index is fetched one item ahead so the atomic's latency overlaps
+  // the current item's arithmetic; a fused check's stop flag is read with it
+  // (device-scope load, so another wave's store is seen).
+  const bool spread = total >= 8 * (int64_t)gridDim.x || 4 * big_total <= total ||
+                      uniform(A.s.big[0].items) == 1;  // then no pair is split
+  const unsigned n_queues = !spread ? 1u : gridDim.x < kQueues ? gridDim.x : kQueues;
+  const unsigned queue = blockIdx.x % n_queues;
+  unsigned long long* const my_counter = A.s.counter + queue * kQueueStride;
   unsigned long long wnext = blockIdx.x;
   int stopnext = 0;
   if (lane == 0 && A.out.stop)
@@ -908,7 +925,7 @@ __global__ __launch_bounds__(kWave, (waves_per_simd<Tc, AT, R>())) void ds_persi
     const int64_t w = uniform((int64_t)wnext);  // lane 0's
     if (w >= total || uniform(stopnext)) break;
     if (lane == 0) {
-      wnext = gridDim.x + atomicAdd(A.s.counter, 1ull);
+      wnext = gridDim.x + queue + (unsigned long long)n_queues * atomicAdd(my_counter, 1ull);
       if (A.out.stop)
         stopnext = __hip_atomic_load(A.out.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }

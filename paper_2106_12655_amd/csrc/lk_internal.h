@@ -33,6 +33,9 @@ struct WorkRec {
 // an exclusive prefix of items.  Work index w < big_total is item w of the big
 // pairs; w >= big_total is the batch of `batch` small pairs starting at
 // (w - big_total) * batch.  All counts are device values.
+// Work counters of a launch, in cache lines of their own: thousands of waves on
+// one counter wait for each other's atomics (5 ns each).
+constexpr int kQueues = 16, kQueueStride = 16;
 struct Sched {
   WorkRec* small;               // [cap]
   WorkRec* big_in;              // [cap] unsorted (filled by plan)
@@ -40,7 +43,7 @@ struct Sched {
   int64_t* big_prefix;          // [cap + 1]
   int32_t* counts;              // [0] = n_small, [1] = n_big
   int64_t* big_total;           // items of all big pairs
-  unsigned long long* counter;  // work counter
+  unsigned long long* counter;  // kQueues work counters, kQueueStride apart
 };
 
 // Where a pass writes its per-pair results (finalisation happens in the
@@ -367,7 +370,7 @@ hipError_t launch_plan(const PlanArgs& a, int32_t n_loops, const LoopInfo& li, c
 hipError_t launch_finalize_split(const Sched& s, const unsigned long long* acc, const Outs& o,
                                  int64_t n_pairs, hipStream_t st);
 // Sort the big list (largest first), scan its items, set big_total, zero the
-// work counter and (optionally) three int32 of the next pass: its two
+// work counters and (optionally) three int32 of the next pass: its two
 // schedule counts and the refit count that follows them in memory.
 hipError_t launch_sched(const Sched& s, int32_t* zero_counts_next, hipStream_t st);
 // prep, plan (main pass) and sched as one launch, for calls with few pairs.

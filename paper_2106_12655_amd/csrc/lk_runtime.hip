@@ -199,17 +199,16 @@ constexpr size_t kMetaCountsRefit = 8;   // int32[2]: n_small, n_big (refit pass
 constexpr size_t kMetaRefitN = 16;       // int32: pairs queued for refit (follows the above)
 constexpr size_t kMetaBigTotalMain = 24; // int64
 constexpr size_t kMetaBigTotalRefit = 32;
-constexpr size_t kMetaCounterMain = 40;  // uint64 work counters
-constexpr size_t kMetaCounterRefit = 48;
 constexpr size_t kMetaStop = 56;         // int32: fused check's stop flag
 // CROSSINGS: the FP64 crossing count refits first and queues what it cannot
 // decide for the FP64 direct sum (a second refit pass)
 constexpr size_t kMetaCountsRefit2 = 64; // int32[2]
 constexpr size_t kMetaRefitN2 = 72;      // int32 (follows the above)
 constexpr size_t kMetaBigTotalRefit2 = 80;
-constexpr size_t kMetaCounterRefit2 = 88;
 constexpr size_t kMetaOffsetsBad = 96;  // int32: offsets that decrease (set by a check)
-constexpr size_t kMetaBytes = 104;
+constexpr size_t kMetaCounters = 256;    // uint64 work counters of the three passes
+constexpr size_t kMetaCounterBytes = 8 * (size_t)lk::kQueues * lk::kQueueStride;
+constexpr size_t kMetaBytes = kMetaCounters + 3 * kMetaCounterBytes;
 
 // Fused certificate check of a call (lk_direct_sum_check); empty for
 // lk_direct_sum.
@@ -267,10 +266,9 @@ lk::Sched make_sched(const Ws& W, int64_t n_pairs, int pass) {
   S.big_prefix = W.big_prefix;
   const size_t counts[3] = {kMetaCountsMain, kMetaCountsRefit, kMetaCountsRefit2};
   const size_t totals[3] = {kMetaBigTotalMain, kMetaBigTotalRefit, kMetaBigTotalRefit2};
-  const size_t counters[3] = {kMetaCounterMain, kMetaCounterRefit, kMetaCounterRefit2};
   S.counts = W.at<int32_t>(counts[pass]);
   S.big_total = W.at<int64_t>(totals[pass]);
-  S.counter = W.at<unsigned long long>(counters[pass]);
+  S.counter = W.at<unsigned long long>(kMetaCounters + (size_t)pass * kMetaCounterBytes);
   return S;
 }
 
