@@ -70,7 +70,8 @@ static_assert(sizeof(BhNode) == 45 * sizeof(double), "BhNode is c, e, M, D, Q ba
 template <typename Tin>
 __global__ __launch_bounds__(64) void bh_leaves_k(BhArgs A) {
   __shared__ double sd[kBhLeaf][8];  // per segment: s[3], d[3]
-  if (blockIdx.x == 0 && threadIdx.x < kBhMaxIters + 3) A.counts[threadIdx.x] = 0;
+  if (blockIdx.x == 0)
+    for (int k = threadIdx.x; k < kBhCounts; k += 64) A.counts[k] = 0;
   const Tin* X = static_cast<const Tin*>(A.xyz);
   const int lane = threadIdx.x;
   const int64_t n_slots = level_slots(A, 0);
@@ -534,7 +535,9 @@ __global__ __launch_bounds__(256) void bh_adapt_k(BhArgs A, int64_t n_pairs, dou
                                                   double beta_max) {
   // the second traversal's lists and leaf list start empty (the count of
   // pairs evaluated again, at kBhMaxIters + 2, was cleared by the leaf kernel)
-  if (blockIdx.x == 0 && threadIdx.x < kBhMaxIters + 2) A.counts[threadIdx.x] = 0;
+  if (blockIdx.x == 0)
+    for (int k = threadIdx.x; k < kBhCounts; k += 256)
+      if (k != kBhMaxIters + 2) A.counts[k] = 0;
   for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < n_pairs;
        p += (int64_t)gridDim.x * 256) {
     double b = 0.0;

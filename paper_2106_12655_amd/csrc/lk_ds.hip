@@ -562,7 +562,8 @@ __device__ __forceinline__ void make_segs(const V3<Tc>* k, Segs<Tc, R>& sg) {
 // 123 TFLOP/s at 90 FLOP a term).
 // `sink` takes the sums of four steps in the compute type, then those of the
 // last steps one by one; added up in that order in FP64 they are the lane's sum.
-template <typename Tc, int AT, int R, typename Sink>
+// EACH: it takes the steps' sums instead.
+template <typename Tc, int AT, int R, bool EACH = false, typename Sink>
 __device__ __forceinline__ void walk(const Vtx<Tc>* l, const Vtx<Tc>* le, bool first,
                                      const Segs<Tc, R>& sg, const Sink& sink) {
   if (l + 4 <= le) {
@@ -578,9 +579,12 @@ __device__ __forceinline__ void walk(const Vtx<Tc>* l, const Vtx<Tc>* le, bool f
         Tc X[R], Y[R];
         vn = {l[q + 2].x, l[q + 2].y, l[q + 2].z};  // the next step's
         walk_xy(wk, v1, sg, X, Y);
-        s4 += step_angles<Tc, AT, R>(X, Y);
+        if constexpr (EACH)
+          sink(step_angles<Tc, AT, R>(X, Y));
+        else
+          s4 += step_angles<Tc, AT, R>(X, Y);
       }
-      sink(s4);
+      if constexpr (!EACH) sink(s4);
     }
   }
   if (l < le) {
@@ -1231,20 +1235,31 @@ __global__ __launch_bounds__(kWave * kTeam<Tc>, (sizeof(Tc) == 4 ? 4 : 2)) void 
 // over their kBhLeaf x kBhLeaf segment pairs with the walk above.  Like the
 // packed small pairs of the direct sum, a wave takes four leaf pairs at a
 // time, 16 lanes each: a lane holds 4 consecutive segments of the B leaf, the
-// A leaf's vertices are in LDS (FP32 terms, FP64 sums).  A wave works through
-// 32 consecutive entries of the list and adds one sum per run of entries of
-// the same pair into its fixed-point accumulator.
+// A leaf's vertices are in LDS (FP32 terms, FP64 sums).  A wave takes eight
+// consecutive entries of the list at a time from sixteen queues (as
+// ds_persistent: on a fixed stride the waves ended at very different times, at
+// 73% of their seats) and adds one sum per run of entries of the same pair into
+// its fixed-point accumulator.  ALU-bound: 11,000 vector instructions a wave and
+// round at 2.5 cycles a SIMD.  840,000 leaf pairs (knit, 200 yarns) took 5,270 us
+// with the walk of two waves a SIMD, 3,800 with its parts of four steps not
+// unrolled, 3,320 on a fixed stride of 32 entries, 3,070 so.
 template <typename Tin>
-__global__ __launch_bounds__(kWave) void bh_near_k(BhArgs A) {
+__global__ __launch_bounds__(kWave, 4) void bh_near_k(BhArgs A) {
   constexpr int K = 4, S = kWave / K, R = 4;  // S * R == kBhLeaf
   static_assert(S * R == kBhLeaf, "a segment of S lanes covers one leaf");
-  __shared__ Vtx<float> lds[K][kBhLeaf + 1];
+  __shared__ Vtx<float> lds[K][kBhLeaf + 2];  // the walk reads a vertex ahead
   const int lane = threadIdx.x, seg = lane / S, sl = lane - seg * S;
   const Tin* X = static_cast<const Tin*>(A.xyz);
   const int64_t cnt = A.counts[kBhMaxIters + 1];
   const int64_t n = cnt < A.near_cap ? cnt : A.near_cap;
-  constexpr int kChunk = 32;
-  for (int64_t c0 = (int64_t)blockIdx.x * kChunk; c0 < n; c0 += (int64_t)gridDim.x * kChunk) {
+  constexpr int kChunk = 8;
+  const unsigned queue = blockIdx.x % kQueues;  // the grid is a multiple of kQueues
+  int32_t* const my_counter = A.counts + kBhQueues + queue * kBhQueueStride;
+  int64_t next = blockIdx.x;
+  for (;;) {
+    const int64_t c0 = uniform(next) * kChunk;  // lane 0's
+    if (c0 >= n) break;
+    if (lane == 0) next = gridDim.x + queue + (int64_t)kQueues * atomicAdd(my_counter, 1);
     const int64_t c1 = (c0 + kChunk) < n ? c0 + kChunk : n;
     double run = 0.0;  // uniform over the wave
     int32_t pr = -1;
@@ -1287,16 +1302,9 @@ __global__ __launch_bounds__(kWave) void bh_near_k(BhArgs A) {
       }
       __syncthreads();
       double acc = 0.0;
-      if (has) {
-        Walk<float, R> wk;
-        walk_init(wk, V3<float>{lds[seg][0].x, lds[seg][0].y, lds[seg][0].z}, sg, true);
-        for (int jj = 0; jj < ma; ++jj) {
-          const Vtx<float> v1 = lds[seg][jj + 1];
-          float X[R], Y[R];
-          walk_xy(wk, V3<float>{v1.x, v1.y, v1.z}, sg, X, Y);
-          acc += (double)step_angles<float, 2, R>(X, Y);
-        }
-      }
+      if (has)
+        walk<float, 2, R, true>(lds[seg], lds[seg] + ma, true, sg,
+                                [&](float sum) { acc += (double)sum; });
 #pragma unroll
       for (int o = S / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
       // the K entries in order: extend the run or flush it (uniform logic)

@@ -246,6 +246,10 @@ constexpr int kBhLeaf = 64;
 constexpr int kBhArity = 8;
 constexpr int kBhMaxLevels = 10;
 constexpr int kBhMaxIters = 2 * kBhMaxLevels;
+// Layout of the counts: the queues' counters are in cache lines of their own.
+constexpr int kBhQueues = 32, kBhQueueStride = 32;
+constexpr int kBhCounts = kBhQueues + kQueues * kBhQueueStride;
+static_assert(kBhMaxIters + 3 <= kBhQueues, "the counts fit before the queues");
 
 // Box centre and half extents (R = |e|, half the box diagonal), and the
 // moments about the centre: c_M, C_D[p][b], C_Q[p][b][c] (row-major).
@@ -272,8 +276,9 @@ struct BhArgs {
   BhPair* list[2];                   // ping-pong node-pair lists
   BhPair* near;                      // leaf pairs for the direct sum
   int64_t list_cap, near_cap;
-  int32_t* counts;                   // [kBhMaxIters + 3]: list entries per iteration, near
-                                     // pairs, pairs evaluated again at a larger beta
+  int32_t* counts;                   // list entries per iteration, near pairs, pairs
+                                     // evaluated again at a larger beta [kBhMaxIters + 3];
+                                     // from kBhQueues the leaf pairs' work queues
   unsigned long long* acc;           // per-pair fixed point [n_pairs][2]
   // adaptive beta (Sec. 3.4.4): the first traversal sums each pair's
   // next-order error estimate into est (fixed point [n_pairs][2]); the second

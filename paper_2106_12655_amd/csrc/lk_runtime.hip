@@ -701,7 +701,7 @@ lk_status bh_prepare(lk_ctx* ctx, const int64_t* off, int32_t n_loops, int64_t n
                    sizeof(lk::BhPair) * (size_t)(2 * Y.list_cap + Y.near_cap))) != LK_OK)
     return st;
   if ((st = ensure(ctx, ctx->bh_adapt, 24 * (size_t)(n_pairs + 1))) != LK_OK) return st;
-  return ensure(ctx, ctx->bh_counts, 4 * (size_t)(lk::kBhMaxIters + 3));
+  return ensure(ctx, ctx->bh_counts, 4 * (size_t)lk::kBhCounts);
 }
 
 // ------------------------------------------------------- pair search buffers
@@ -1766,7 +1766,7 @@ int64_t ctx_workspace_need(int mode, int32_t n_loops, int64_t n_pairs, int64_t n
     const BhLayout Y = bh_layout(n_vertices, n_loops, n_pairs);
     b += (double)sizeof(BhNode) * (double)Y.nodes +
          (double)sizeof(BhPair) * (double)(2 * Y.list_cap + Y.near_cap) + 24.0 * (P + 1) +
-         4.0 * (kBhMaxIters + 3);
+         4.0 * kBhCounts;
   }
   return (int64_t)(1.25 * b);  // ensure() allocates a quarter more than asked
 }
