@@ -17,14 +17,14 @@
 namespace lk {
 namespace {
 
-// Largest loop i with (off[i] - off[0]) / span + i <= slot.
+// Largest loop i with (off[i] - off[0]) / 2^shift + i <= slot.
 __device__ __forceinline__ int32_t find_loop(const int64_t* off, int32_t L, int64_t slot,
-                                             int64_t span) {
+                                             int shift) {
   const int64_t o0 = off[0];
   int32_t lo = 0, hi = L;
   while (hi - lo > 1) {
     const int32_t mid = (lo + hi) >> 1;
-    if ((off[mid] - o0) / span + mid <= slot)
+    if (((off[mid] - o0) >> shift) + mid <= slot)
       lo = mid;
     else
       hi = mid;
@@ -33,12 +33,12 @@ __device__ __forceinline__ int32_t find_loop(const int64_t* off, int32_t L, int6
 }
 
 __device__ __forceinline__ int64_t node_slot(const BhArgs& A, int32_t loop, int h, int64_t k) {
-  return A.level_base[h] + (A.off[loop] - A.off[0]) / bh_span(h) + loop + k;
+  return A.level_base[h] + ((A.off[loop] - A.off[0]) >> bh_shift(h)) + loop + k;
 }
 
 // Slots of level h that the device offsets need.
 __device__ __forceinline__ int64_t level_slots(const BhArgs& A, int h) {
-  return (A.off[A.n_loops] - A.off[0]) / bh_span(h) + A.n_loops + 1;
+  return ((A.off[A.n_loops] - A.off[0]) >> bh_shift(h)) + A.n_loops + 1;
 }
 
 // Lowest level with a single node for a loop of n segments.
@@ -82,9 +82,9 @@ __global__ __launch_bounds__(64) void bh_leaves_k(BhArgs A) {
   const int mb = j < 12 ? jd % 3 : (jq / 3) % 3;
   const int mc = jq % 3;
   for (int64_t slot = blockIdx.x; slot < n_slots; slot += gridDim.x) {
-    const int32_t i = find_loop(A.off, A.n_loops, slot, kBhLeaf);
+    const int32_t i = find_loop(A.off, A.n_loops, slot, bh_shift(0));
     const int64_t oi = A.off[i], n = A.off[i + 1] - oi;
-    const int64_t k = slot - ((oi - A.off[0]) / kBhLeaf + i);
+    const int64_t k = slot - (((oi - A.off[0]) >> bh_shift(0)) + i);
     // (offsets that decrease make no node: every read stays in the loop)
     if (n <= 0 || k < 0 || k >= bh_count(n, 0)) continue;  // uniform over the workgroup
     const int64_t a = k * kBhLeaf;
@@ -177,12 +177,12 @@ __global__ __launch_bounds__(64) void bh_leaves_k(BhArgs A) {
 //   C_Q[p][b][c] += C_Qc[p][b][c] + C_Dc[p][b] r_c + C_Dc[p][c] r_b + c_Mc[p] r_b r_c.
 __global__ __launch_bounds__(256) void bh_level_k(BhArgs A, int h) {
   const int64_t n_slots = level_slots(A, h);
-  const int64_t span = bh_span(h);
+  const int shift = bh_shift(h);
   for (int64_t slot = (int64_t)blockIdx.x * 256 + threadIdx.x; slot < n_slots;
        slot += (int64_t)gridDim.x * 256) {
-    const int32_t i = find_loop(A.off, A.n_loops, slot, span);
+    const int32_t i = find_loop(A.off, A.n_loops, slot, shift);
     const int64_t n = A.off[i + 1] - A.off[i];
-    const int64_t k = slot - ((A.off[i] - A.off[0]) / span + i);
+    const int64_t k = slot - (((A.off[i] - A.off[0]) >> shift) + i);
     const int64_t nch = bh_count(n, h - 1);
     if (n <= 0 || k < 0 || k >= bh_count(n, h) || nch <= 1) continue;  // no such node, or above the root
     if (slot >= A.level_cap[h]) continue;
@@ -343,23 +343,6 @@ __device__ double far_estimate(const BhNode& u, const BhNode& v) {
 }
 
 // ------------------------------------------------------------ traversal
-// Wave-collective append of `n` entries per lane to a list: returns the
-// lane's first position (one atomic per wave).
-__device__ __forceinline__ int64_t wave_reserve(int32_t* count, int n) {
-  const int lane = threadIdx.x & 63;
-  int32_t x = n;  // inclusive scan
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int32_t y = __shfl_up(x, o);
-    if (lane >= o) x += y;
-  }
-  const int32_t total = __shfl(x, 63);
-  int32_t b0 = 0;
-  if (total > 0 && lane == 0) b0 = atomicAdd(count, total);
-  b0 = __shfl(b0, 0);
-  return (int64_t)b0 + x - n;
-}
-
 // Node (level h, index k) of loop `loop`: its slot, or -1 beyond the buffer.
 __device__ __forceinline__ int64_t checked_slot(const BhArgs& A, int32_t loop, int h, int64_t k) {
   const int64_t s = node_slot(A, loop, h, k);
@@ -381,140 +364,152 @@ __device__ __forceinline__ bool is_far(double beta, const BhNode& u, const BhNod
 // is split (the node with children and the larger radius); its child pairs
 // are classified at once, so the next step's list holds only pairs that must
 // be split again.
-__global__ __launch_bounds__(256) void bh_expand_k(BhArgs A, int it) {
-  const int lane = threadIdx.x & 63;
+// A lane per child (eight lanes a node pair): a child's node is read by one lane
+// and the other node by eight at once, and what is far is evaluated by lanes side
+// by side.  With a thread per pair that took its children one after the other, an
+// atomic a wave and list, and 64-bit divisions by the nodes' spans, the steps of
+// 478,000 pairs with 2.5 million far children took 1,110 us together; now 450.
+// Bound by the scattered reads of nodes (360 bytes): three or four waves a SIMD
+// (248 registers give two) change the call by less than 1%.
+constexpr int kExpandWaves = 4, kExpandPairs = 64 * kExpandWaves / kBhArity;
+struct FarJob {
+  int32_t u, v, p;  // node slots, pair
+};
+
+__global__ __launch_bounds__(64 * kExpandWaves) void bh_expand_k(BhArgs A, int it) {
+  static_assert(64 % kBhArity == 0, "the lanes of a node pair are in one wave");
+  __shared__ FarJob jobs[64 * kExpandWaves];
+  __shared__ int n_jobs[2];  // of this pass and the next
+  __shared__ int32_t offset[2][kExpandWaves], base_of[2];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, c = threadIdx.x % kBhArity;
   const BhPair* in = A.list[it & 1];
   BhPair* out = A.list[(it + 1) & 1];
-  int32_t* n_out = &A.counts[it + 1];
-  int32_t* n_near = &A.counts[kBhMaxIters + 1];
   const int64_t n_in = A.counts[it] < A.list_cap ? A.counts[it] : A.list_cap;
-  const int64_t stride = (int64_t)gridDim.x * 256;
-  // the same trip count in every lane (the appends are wavefront-collective)
-  for (int64_t base = (int64_t)blockIdx.x * 256; base < n_in; base += stride) {
-    const int64_t e = base + threadIdx.x;
+  if (threadIdx.x == 0) n_jobs[0] = 0;
+  __syncthreads();
+  int pass = 0;
+  // the same trip count in every thread (the appends are collective)
+  for (int64_t base = (int64_t)blockIdx.x * kExpandPairs; base < n_in;
+       base += (int64_t)gridDim.x * kExpandPairs, pass ^= 1) {
+    const int64_t e = base + threadIdx.x / kBhArity;
     const bool has = e < n_in;
-    const BhPair w = has ? in[e] : BhPair{-1, 0, 0, 0};
-    double val = 0.0, err = 0.0;
-    bool fail = false;
-    const double beta = has && A.beta_p ? A.beta_p[w.p] : A.beta;
-    // classification of the pair itself (roots arrive unclassified), then of
-    // its children: bit c of near_m / next_m marks child c for that list
-    int self = 0;  // 0 none, 1 near, 2 split
-    unsigned near_m = 0u, next_m = 0u;
-    int split_a = 0, hc = 0;
-    int64_t cbase = 0;
+    const BhPair w = in[has ? e : base];
+    const double beta = A.beta_p ? A.beta_p[w.p] : A.beta;
+    // what becomes of this lane's child (of the pair itself: lane 0's)
+    bool far = false, near = false, next = false, fail = false;
+    int64_t su = -1, sv = -1;
+    BhPair ch = w;
     if (has) {
       const int ha = w.lev & 255, hb = w.lev >> 8;
       const int32_t i = A.pairs[2 * (int64_t)w.p], j = A.pairs[2 * (int64_t)w.p + 1];
-      const int64_t sa = checked_slot(A, i, ha, w.ka), sb = checked_slot(A, j, hb, w.kb);
-      if (sa < 0 || sb < 0) {
+      su = checked_slot(A, i, ha, w.ka);
+      sv = checked_slot(A, j, hb, w.kb);
+      if (su < 0 || sv < 0) {
         fail = true;
+      } else if (is_far(beta, A.nodes[su], A.nodes[sv])) {
+        far = c == 0;
+      } else if (ha == 0 && hb == 0) {
+        near = c == 0;
       } else {
-        const BhNode& u = A.nodes[sa];
-        const BhNode& v = A.nodes[sb];
-        if (is_far(beta, u, v)) {
-          val = far_field(u, v, A.order);
-          if (A.est) err = far_estimate(u, v);
-        } else if (ha == 0 && hb == 0) {
-          self = 1;
-        } else {
-          self = 2;
-          split_a = ha > 0 && (hb == 0 || node_radius(u) > node_radius(v));
-          const int32_t loop = split_a ? i : j;
-          const int64_t n = A.off[loop + 1] - A.off[loop];
-          hc = (split_a ? ha : hb) - 1;
-          const int64_t cnt = bh_count(n, hc);
-          cbase = (int64_t)(split_a ? w.ka : w.kb) * kBhArity;
-          const int64_t c1 = (cbase + kBhArity) < cnt ? cbase + kBhArity : cnt;
-          for (int c = 0; c < (int)(c1 - cbase); ++c) {
-            const int64_t sc = checked_slot(A, loop, hc, cbase + c);
-            if (sc < 0) {
-              fail = true;
-              break;
-            }
-            const BhNode& ch = A.nodes[sc];
-            const bool far = split_a ? is_far(beta, ch, v) : is_far(beta, u, ch);
-            if (far) {
-              val += split_a ? far_field(ch, v, A.order) : far_field(u, ch, A.order);
-              if (A.est) err += split_a ? far_estimate(ch, v) : far_estimate(u, ch);
-            } else if (hc == 0 && (split_a ? hb : ha) == 0) {
-              near_m |= 1u << c;
-            } else {
-              next_m |= 1u << c;
-            }
+        const bool split_a =
+            ha > 0 && (hb == 0 || node_radius(A.nodes[su]) > node_radius(A.nodes[sv]));
+        const int32_t loop = split_a ? i : j;
+        const int hc = (split_a ? ha : hb) - 1;
+        const int64_t k = (int64_t)(split_a ? w.ka : w.kb) * kBhArity + c;
+        if (k < bh_count(A.off[loop + 1] - A.off[loop], hc)) {
+          const int64_t sc = checked_slot(A, loop, hc, k);
+          if (split_a) {
+            su = sc;
+            ch.ka = (int32_t)k;
+            ch.lev = hc | (hb << 8);
+          } else {
+            sv = sc;
+            ch.kb = (int32_t)k;
+            ch.lev = ha | (hc << 8);
           }
+          if (sc < 0)
+            fail = true;
+          else if (is_far(beta, A.nodes[su], A.nodes[sv]))
+            far = true;
+          else if (ch.lev == 0)
+            near = true;
+          else
+            next = true;
         }
       }
     }
-    if (fail) atomicOr(&A.out.flags[w.p], kFlagNonfinite);  // refitted
-    // far-field values (and estimates): one fixed-point add per pair present
-    // in the wave
-    const bool add = (val != 0.0 || err != 0.0) && !fail;
-    unsigned long long rem = __ballot(add);
-    while (rem) {
-      const int leader = __ffsll((long long)rem) - 1;
-      const int32_t pl = __shfl(w.p, leader);
-      const bool mine = add && w.p == pl;
-      const unsigned long long m = __ballot(mine);
-      const double sum = wave_sum(mine ? val : 0.0);
-      const double esum = A.est ? wave_sum(mine ? err : 0.0) : 0.0;
-      if (lane == leader) {
-        if (fabs(sum) < 1.0e14)
-          fixed_add(&A.acc[2 * (int64_t)pl], sum);
-        else
-          atomicOr(&A.out.flags[pl], kFlagNonfinite);  // NaN or absurd: refitted
-        if (A.est && esum < 1.0e14) fixed_add(&A.est[2 * (int64_t)pl], esum);
+    // a pair with a node beyond the buffer is refitted as a whole
+    const unsigned long long failed = __ballot(fail);
+    if (failed) {
+      if (fail) atomicOr(&A.out.flags[w.p], kFlagNonfinite);
+      if (failed >> (lane & ~(kBhArity - 1)) & ((1u << kBhArity) - 1)) far = near = next = false;
+    }
+    // the workgroup's appends: one atomic a list
+    const unsigned long long mn = __ballot(near), mx = __ballot(next), mf = __ballot(far);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    int at_job = 0;
+    if (lane == 0) {
+      offset[0][wv] = __popcll(mn);
+      offset[1][wv] = __popcll(mx);
+      if (mf) at_job = atomicAdd(&n_jobs[pass], __popcll(mf));
+    }
+    if (mf) {
+      at_job = __shfl(at_job, 0);
+      if (far) jobs[at_job + __popcll(mf & below)] = FarJob{(int32_t)su, (int32_t)sv, w.p};
+    }
+    __syncthreads();
+    if (threadIdx.x == 2) n_jobs[pass ^ 1] = 0;
+    if (threadIdx.x < 2) {
+      int32_t n = 0;
+      for (int q = 0; q < kExpandWaves; ++q) {
+        const int32_t m = offset[threadIdx.x][q];
+        offset[threadIdx.x][q] = n;
+        n += m;
       }
-      rem &= ~m;
+      base_of[threadIdx.x] =
+          n ? atomicAdd(&A.counts[threadIdx.x ? it + 1 : kBhMaxIters + 1], n) : 0;
     }
-    if (fail) {
-      self = 0;
-      near_m = next_m = 0u;
-    }
-    // leaf pairs to the direct sum
-    const int n_near_me = (self == 1 ? 1 : 0) + __popc(near_m);
-    int64_t at = wave_reserve(n_near, n_near_me);
+    __syncthreads();
     bool over = false;
-    if (n_near_me > 0) {
-      const int ha = w.lev & 255, hb = w.lev >> 8;
-      if (self == 1) {
-        if (at < A.near_cap) A.near[at] = w; else over = true;
-        ++at;
-      }
-      for (int c = 0; c < kBhArity; ++c) {
-        if (!(near_m >> c & 1u)) continue;
-        BhPair ch = w;
-        if (split_a) {
-          ch.ka = (int32_t)(cbase + c);
-          ch.lev = hc | (hb << 8);
-        } else {
-          ch.kb = (int32_t)(cbase + c);
-          ch.lev = ha | (hc << 8);
-        }
-        if (at < A.near_cap) A.near[at] = ch; else over = true;
-        ++at;
-      }
+    if (near) {
+      const int64_t at = (int64_t)base_of[0] + offset[0][wv] + __popcll(mn & below);
+      if (at < A.near_cap) A.near[at] = ch; else over = true;
     }
-    // pairs to split again, for the next step
-    const int n_next_me = __popc(next_m);
-    at = wave_reserve(n_out, n_next_me);
-    if (n_next_me > 0) {
-      const int ha = w.lev & 255, hb = w.lev >> 8;
-      for (int c = 0; c < kBhArity; ++c) {
-        if (!(next_m >> c & 1u)) continue;
-        BhPair ch = w;
-        if (split_a) {
-          ch.ka = (int32_t)(cbase + c);
-          ch.lev = hc | (hb << 8);
-        } else {
-          ch.kb = (int32_t)(cbase + c);
-          ch.lev = ha | (hc << 8);
-        }
-        if (at < A.list_cap) out[at] = ch; else over = true;
-        ++at;
-      }
+    if (next) {
+      const int64_t at = (int64_t)base_of[1] + offset[1][wv] + __popcll(mx & below);
+      if (at < A.list_cap) out[at] = ch; else over = true;
     }
     if (over) atomicOr(&A.out.flags[w.p], kFlagNonfinite);  // a list was full: refitted
+    // far pairs, on as few waves as they fill
+    const int n_far = n_jobs[pass];
+    if (wv * 64 < n_far) {
+      const bool mine = (int)threadIdx.x < n_far;
+      const FarJob f = jobs[mine ? threadIdx.x : wv * 64];
+      double val = 0.0, err = 0.0;
+      if (mine) {
+        val = far_field(A.nodes[f.u], A.nodes[f.v], A.order);
+        if (A.est) err = far_estimate(A.nodes[f.u], A.nodes[f.v]);
+      }
+      // values (and estimates): one fixed-point add per pair present in the wave
+      unsigned long long rem = __ballot(mine && (val != 0.0 || err != 0.0));
+      while (rem) {
+        const int leader = __ffsll((long long)rem) - 1;
+        const int32_t pl = __shfl(f.p, leader);
+        const bool same = mine && f.p == pl;
+        const unsigned long long m = __ballot(same);
+        const double sum = wave_sum(same ? val : 0.0);
+        const double esum = A.est ? wave_sum(same ? err : 0.0) : 0.0;
+        if (lane == leader) {
+          if (fabs(sum) < 1.0e14)
+            fixed_add(&A.acc[2 * (int64_t)pl], sum);
+          else
+            atomicOr(&A.out.flags[pl], kFlagNonfinite);  // NaN or absurd: refitted
+          if (A.est && esum < 1.0e14) fixed_add(&A.est[2 * (int64_t)pl], esum);
+        }
+        rem &= ~m;
+      }
+    }
+    __syncthreads();  // the jobs are read
   }
 }
 
@@ -584,7 +579,7 @@ hipError_t launch_bh_roots(const BhArgs& a, int64_t n_pairs, hipStream_t s) {
 }
 
 hipError_t launch_bh_expand(const BhArgs& a, int it, hipStream_t s) {
-  bh_expand_k<<<2048, 256, 0, s>>>(a, it);
+  bh_expand_k<<<2048, 64 * kExpandWaves, 0, s>>>(a, it);
   return hipGetLastError();
 }
 

@@ -293,14 +293,12 @@ struct BhArgs {
   Outs out;
 };
 
-__device__ __forceinline__ int64_t bh_span(int h) {
-  int64_t s = kBhLeaf;
-  for (int q = 0; q < h; ++q) s *= kBhArity;
-  return s;
-}
+// kBhLeaf kBhArity^h segments are 2^bh_shift(h): shifts for the quotients, which
+// the tree kernels take several times per node pair.
+static_assert(kBhLeaf == 1 << 6 && kBhArity == 1 << 3, "node spans are powers of two");
+__device__ __forceinline__ int bh_shift(int h) { return 6 + 3 * h; }
 __device__ __forceinline__ int64_t bh_count(int64_t n, int h) {
-  const int64_t s = bh_span(h);
-  return (n + s - 1) / s;
+  return (n + ((int64_t)1 << bh_shift(h)) - 1) >> bh_shift(h);
 }
 
 // Tree build (one launch for the leaves, one per level above).
