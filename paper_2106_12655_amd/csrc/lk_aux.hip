@@ -519,9 +519,12 @@ __global__ __launch_bounds__(1024) void sched_k(Sched S, int32_t* zero_next) {
 }
 
 // General single-workgroup exclusive scan (pair search, verification).
-__global__ __launch_bounds__(1024) void scan_k(const int64_t* counts, int64_t n, int64_t* prefix) {
+__global__ __launch_bounds__(1024) void scan_k(const int64_t* counts, int64_t n, int64_t* prefix,
+                                               int64_t* host_total) {
   __shared__ int64_t wsum[16];
-  block_scan_array(counts, n, prefix, wsum);
+  const int64_t total = block_scan_array(counts, n, prefix, wsum);
+  if (threadIdx.x == 0)
+    __hip_atomic_store(host_total, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ------------------------------------------------------ potential link search
@@ -1364,8 +1367,9 @@ hipError_t launch_zero_i64(int64_t* p, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_scan(const int64_t* counts, int64_t n, int64_t* prefix, hipStream_t s) {
-  scan_k<<<1, 1024, 0, s>>>(counts, n, prefix);
+hipError_t launch_scan(const int64_t* counts, int64_t n, int64_t* prefix, int64_t* host_total,
+                       hipStream_t s) {
+  scan_k<<<1, 1024, 0, s>>>(counts, n, prefix, host_total);
   return hipGetLastError();
 }
 

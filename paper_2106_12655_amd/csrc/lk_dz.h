@@ -49,6 +49,7 @@ struct DzArgs {
   int32_t* pair_ab;        // [P][2] the pair as (a, b), a the side of more groups
   uint64_t* part;          // scan partials, one per block
   uint64_t* totals;        // [0] packed (pieces << 32 | unprocessed) after the split
+  int64_t* host;           // the same, for the host (memory the device can write)
   uint32_t* lflags;        // [L]
   double* lsum;            // [L] sums of |coordinate| per loop
   double* lim2;            // [1] (eps * xi)^2
@@ -56,7 +57,10 @@ struct DzArgs {
 };
 
 // *bad (device int32, set to 0 by the caller) becomes 1 if the offsets decrease.
-hipError_t launch_dz_check(const int64_t* off, int32_t n_loops, int32_t* bad, hipStream_t s);
+// host[kHostFirst], [kHostLast]: the first and last offset; [kHostBad] = 1 if they
+// decrease anywhere (host memory the device can write, clear before the launch).
+constexpr int kHostFirst = 1, kHostLast = 2, kHostBad = 3;
+hipError_t launch_dz_check(const int64_t* off, int32_t n_loops, int64_t* host, hipStream_t s);
 hipError_t launch_dz_setup(const DzArgs& a, int64_t n_points, hipStream_t s);
 hipError_t launch_dz_pass(const DzArgs& a, int n_cu, hipStream_t s);
 hipError_t launch_dz_finish(const DzArgs& a, double* xyz_out, int64_t capacity,

@@ -76,7 +76,8 @@ __device__ uint64_t block_sum(uint64_t v) {
 // Exclusive scan of part[0, nb) in place (one block of 1024 threads); the sum
 // goes to *total.
 __global__ __launch_bounds__(1024) void dz_scan_part_k(uint64_t* part, int64_t nb,
-                                                       uint64_t* total, int64_t* total_i64) {
+                                                       uint64_t* total, int64_t* total_i64,
+                                                       int64_t* host) {
   uint64_t carry = 0;
   for (int64_t base = 0; base < nb; base += blockDim.x) {
     const int64_t i = base + threadIdx.x;
@@ -89,6 +90,8 @@ __global__ __launch_bounds__(1024) void dz_scan_part_k(uint64_t* part, int64_t n
   if (threadIdx.x == 0) {
     if (total) *total = carry;
     if (total_i64) *total_i64 = (int64_t)carry;
+    if (host)
+      __hip_atomic_store(host, (int64_t)carry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -279,10 +282,15 @@ __global__ __launch_bounds__(kThreads) void dz_loops_k(DzArgs A) {
 // Offsets that decrease anywhere: *bad = 1 (the host rejects the call
 // before any kernel indexes with them).
 __global__ __launch_bounds__(kThreads) void dz_check_offsets_k(const int64_t* off, int32_t L,
-                                                               int32_t* bad) {
+                                                               int64_t* host) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    __hip_atomic_store(host + kHostFirst, off[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(host + kHostLast, off[L], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < L;
        i += (int64_t)gridDim.x * kThreads)
-    if (off[i + 1] < off[i]) *bad = 1;
+    if (off[i + 1] < off[i])
+      __hip_atomic_store(host + kHostBad, (int64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // xi = mean over the points of (|x| + |y| + |z|) / 3; lim2 = (eps * xi)^2.
@@ -596,9 +604,9 @@ int64_t blocks_for(int64_t n) { return (n + kThreads - 1) / kThreads; }
 
 }  // namespace
 
-hipError_t launch_dz_check(const int64_t* off, int32_t n_loops, int32_t* bad, hipStream_t s) {
+hipError_t launch_dz_check(const int64_t* off, int32_t n_loops, int64_t* host, hipStream_t s) {
   const int64_t b = blocks_for(n_loops);
-  dz_check_offsets_k<<<(unsigned)(b < 4096 ? b : 4096), kThreads, 0, s>>>(off, n_loops, bad);
+  dz_check_offsets_k<<<(unsigned)(b < 4096 ? b : 4096), kThreads, 0, s>>>(off, n_loops, host);
   return hipGetLastError();
 }
 
@@ -617,13 +625,13 @@ hipError_t launch_dz_pass(const DzArgs& a, int n_cu, hipStream_t s) {
   const int64_t pb = blocks_for(a.n_pairs);
   if (pb > 0) {
     dz_items_reduce_k<<<(unsigned)pb, kThreads, 0, s>>>(a);
-    dz_scan_part_k<<<1, 1024, 0, s>>>(a.part, pb, nullptr, a.pair_pre + a.n_pairs);
+    dz_scan_part_k<<<1, 1024, 0, s>>>(a.part, pb, nullptr, a.pair_pre + a.n_pairs, nullptr);
     dz_items_apply_k<<<(unsigned)pb, kThreads, 0, s>>>(a);
     dz_test_k<<<(unsigned)(32 * n_cu), kThreads, 0, s>>>(a);
   }
   const int64_t qb = blocks_for(a.n);
   dz_split_reduce_k<<<(unsigned)qb, kThreads, 0, s>>>(a);
-  dz_scan_part_k<<<1, 1024, 0, s>>>(a.part, qb, a.totals, nullptr);
+  dz_scan_part_k<<<1, 1024, 0, s>>>(a.part, qb, a.totals, nullptr, a.host);
   dz_split_apply_k<<<(unsigned)qb, kThreads, 0, s>>>(a);
   dz_offsets_k<<<(unsigned)blocks_for(a.n_loops + 1), kThreads, 0, s>>>(a);
   return hipGetLastError();

@@ -393,8 +393,10 @@ hipError_t launch_finalize_replan(const Sched& s, const unsigned long long* acc,
                                   const Sched& sr, int32_t* zero_counts_next, hipStream_t st);
 // *p = 0 with a kernel (safe inside a captured sequence).
 hipError_t launch_zero_i64(int64_t* p, hipStream_t s);
-// Exclusive scan of counts[0..n) into prefix[0..n] (single workgroup).
-hipError_t launch_scan(const int64_t* counts, int64_t n, int64_t* prefix, hipStream_t s);
+// Exclusive scan of counts[0..n) into prefix[0..n] (single workgroup); the total
+// goes to *host_total too (host memory the device can write).
+hipError_t launch_scan(const int64_t* counts, int64_t n, int64_t* prefix, int64_t* host_total,
+                       hipStream_t s);
 // Potential link search: boxes (also clears the tiles' pair counts), the grid
 // (optional), then the rows of the pair list.
 hipError_t launch_boxes(const void* xyz, bool in_f64, const int64_t* off, int32_t n_loops,

@@ -205,7 +205,6 @@ constexpr size_t kMetaStop = 56;         // int32: fused check's stop flag
 constexpr size_t kMetaCountsRefit2 = 64; // int32[2]
 constexpr size_t kMetaRefitN2 = 72;      // int32 (follows the above)
 constexpr size_t kMetaBigTotalRefit2 = 80;
-constexpr size_t kMetaOffsetsBad = 96;  // int32: offsets that decrease (set by a check)
 constexpr size_t kMetaCounters = 256;    // uint64 work counters of the three passes
 constexpr size_t kMetaCounterBytes = 8 * (size_t)lk::kQueues * lk::kQueueStride;
 constexpr size_t kMetaBytes = kMetaCounters + 3 * kMetaCounterBytes;
@@ -653,6 +652,31 @@ lk_status ensure_workspace(lk_ctx* ctx, int32_t n_loops, int64_t n_pairs, hipStr
   return ensure_partials(ctx, s, have_stream);
 }
 
+// Memory that kernels write and the host reads after a synchronisation.
+lk_status ensure_host(lk_ctx* ctx) {
+  if (ctx->host_total ||
+      hipHostMalloc((void**)&ctx->host_total, 64, hipHostMallocDefault) == hipSuccess)
+    return LK_OK;
+  ctx->host_total = nullptr;
+  return ctx->fail(LK_ENOMEM, "hipHostMalloc failed");
+}
+
+// The entries that the offsets span, and whether they decrease anywhere: one
+// launch and one synchronisation (a fill, three copies to pageable memory and the
+// check took 50 us more).
+lk_status check_offsets(lk_ctx* ctx, const int64_t* off, int32_t n_loops, hipStream_t s,
+                        int64_t* n, bool* bad) {
+  lk_status st = ensure_host(ctx);
+  if (st != LK_OK) return st;
+  volatile int64_t* h = ctx->host_total;
+  h[lk::kHostBad] = 0;
+  LK_HIP(lk::launch_dz_check(off, n_loops, ctx->host_total, s));
+  LK_HIP(hipStreamSynchronize(s));
+  *n = h[lk::kHostLast] - h[lk::kHostFirst];
+  *bad = h[lk::kHostBad] != 0;
+  return LK_OK;
+}
+
 // Crossing count: size the culling boxes for the call's vertex count, which
 // is read from the device (one synchronisation) the first time an offsets
 // array is seen.  Inside a stream capture nothing is read and the boxes keep
@@ -662,19 +686,14 @@ lk_status read_vertices(lk_ctx* ctx, const int64_t* off, int32_t n_loops, hipStr
   if (can_sync && (ctx->cc_off_key != off || ctx->cc_loops_key != n_loops)) {
     // the block and node slots are computed from the offsets, so offsets that
     // decrease are rejected here, in the same synchronisation
-    int64_t ends[2] = {0, 0};
-    int32_t bad = 0;
-    int32_t* bad_d = meta_at<int32_t>(ctx, kMetaOffsetsBad);
-    LK_HIP(hipMemsetAsync(bad_d, 0, 4, s));
-    LK_HIP(lk::launch_dz_check(off, n_loops, bad_d, s));
-    LK_HIP(hipMemcpyAsync(&bad, bad_d, 4, hipMemcpyDeviceToHost, s));
-    LK_HIP(hipMemcpyAsync(&ends[0], off, 8, hipMemcpyDeviceToHost, s));
-    LK_HIP(hipMemcpyAsync(&ends[1], off + n_loops, 8, hipMemcpyDeviceToHost, s));
-    LK_HIP(hipStreamSynchronize(s));
+    int64_t n = 0;
+    bool bad = false;
+    lk_status st = check_offsets(ctx, off, n_loops, s, &n, &bad);
+    if (st != LK_OK) return st;
     if (bad) return ctx->fail(LK_EINVAL, "loop offsets decrease");
     ctx->cc_off_key = off;
     ctx->cc_loops_key = n_loops;
-    ctx->cc_vertices = ends[1] - ends[0] > 0 ? ends[1] - ends[0] : 0;
+    ctx->cc_vertices = n > 0 ? n : 0;
   }
   *v = ctx->cc_off_key == off && ctx->cc_loops_key == n_loops ? ctx->cc_vertices : 0;
   return LK_OK;
@@ -718,11 +737,7 @@ int64_t grid_buckets(int32_t n_loops) {
 lk_status ensure_rows(lk_ctx* ctx, int32_t n_loops) {
   const size_t L = (size_t)n_loops;
   lk_status st;
-  if (!ctx->host_total &&
-      hipHostMalloc((void**)&ctx->host_total, 64, hipHostMallocDefault) != hipSuccess) {
-    ctx->host_total = nullptr;
-    return ctx->fail(LK_ENOMEM, "hipHostMalloc failed");
-  }
+  if ((st = ensure_host(ctx)) != LK_OK) return st;
   if ((st = ensure(ctx, ctx->boxes, 48 * L)) != LK_OK) return st;
   return ensure(ctx, ctx->pls_rows, 8 * (L / lk::kRowTile + 1) + 4 * L * (1 + lk::kRowSlots));
 }
@@ -1346,16 +1361,9 @@ lk_status lk_discretize(lk_ctx* ctx, const double* ctrl, const int64_t* ctrl_off
   const size_t o_lsum = (4 * L + 7) / 8 * 8, o_off = o_lsum + 8 * L;
   const size_t o_tot = o_off + 4 * 8 * (L + 1), o_lim = o_tot + 32;
   if ((st = ensure(ctx, ctx->dz_loops, o_lim + 8)) != LK_OK) return st;
-  int32_t* bad_d = (int32_t*)((char*)ctx->dz_loops.p + o_tot);  // the totals slot, free until the passes
-  int64_t ends[2] = {0, 0};
-  int32_t bad = 0;
-  LK_HIP(hipMemsetAsync(bad_d, 0, 4, s));
-  LK_HIP(lk::launch_dz_check(ctrl_offsets, n_loops, bad_d, s));
-  LK_HIP(hipMemcpyAsync(&bad, bad_d, 4, hipMemcpyDeviceToHost, s));
-  LK_HIP(hipMemcpyAsync(&ends[0], ctrl_offsets, 8, hipMemcpyDeviceToHost, s));
-  LK_HIP(hipMemcpyAsync(&ends[1], ctrl_offsets + n_loops, 8, hipMemcpyDeviceToHost, s));
-  LK_HIP(hipStreamSynchronize(s));
-  const int64_t N = ends[1] - ends[0];
+  int64_t N = 0;
+  bool bad = false;
+  if ((st = check_offsets(ctx, ctrl_offsets, n_loops, s, &N, &bad)) != LK_OK) return st;
   if (bad || N < 0) return ctx->fail(LK_EINVAL, "offsets decrease");
   // piece indices are int32 and the split packs two 32-bit counts
   const int64_t kMaxPieces = (int64_t)1 << 30;
@@ -1428,6 +1436,7 @@ lk_status lk_discretize(lk_ctx* ctx, const double* ctrl, const int64_t* ctrl_off
     a.uoff_cur = offs + (c ? 3 : 1) * (L + 1);
     a.uoff_nxt = offs + (c ? 1 : 3) * (L + 1);
     a.totals = (uint64_t*)(lb + o_tot);
+    a.host = ctx->host_total;
     a.lim2 = (double*)(lb + o_lim);
     a.cap_u = (int64_t)(ctx->dz_pbox.bytes / 48);
     a.pbox = (double*)ctx->dz_pbox.p;
@@ -1450,9 +1459,8 @@ lk_status lk_discretize(lk_ctx* ctx, const double* ctrl, const int64_t* ctrl_off
     if ((st = size_pass(n, nu, cur)) != LK_OK) return st;
     lk::DzArgs a = args(cur, n, nu);
     LK_HIP(lk::launch_dz_pass(a, ctx->n_cu, s));
-    uint64_t tot = 0;
-    LK_HIP(hipMemcpyAsync(&tot, a.totals, 8, hipMemcpyDeviceToHost, s));
     LK_HIP(hipStreamSynchronize(s));
+    const uint64_t tot = (uint64_t)*(volatile int64_t*)ctx->host_total;
     const int64_t n2 = (int64_t)(tot >> 32), nu2 = (int64_t)(tot & 0xffffffffull);
     splits += n2 - n;
     n = n2;
@@ -1497,15 +1505,15 @@ lk_status lk_verify(lk_ctx* ctx, const int32_t* pairs, const int32_t* lk, int64_
   *n_mismatch = 0;
   const int64_t m = n + n_exp;
   if (m == 0) return LK_OK;
+  if ((st = ensure_host(ctx)) != LK_OK) return st;
   if ((st = ensure(ctx, ctx->vcounts, 8 * (size_t)m)) != LK_OK) return st;
   if ((st = ensure(ctx, ctx->vprefix, 8 * (size_t)(m + 1))) != LK_OK) return st;
   int64_t* flag = (int64_t*)ctx->vcounts.p;
   int64_t* pre = (int64_t*)ctx->vprefix.p;
   LK_HIP(lk::launch_verify(pairs, lk, n, exp_pairs, exp_lk, n_exp, flag, s));
-  LK_HIP(lk::launch_scan(flag, m, pre, s));
-  int64_t total = 0;
-  LK_HIP(hipMemcpyAsync(&total, pre + m, 8, hipMemcpyDeviceToHost, s));
+  LK_HIP(lk::launch_scan(flag, m, pre, ctx->host_total, s));
   LK_HIP(hipStreamSynchronize(s));
+  int64_t total = *(volatile int64_t*)ctx->host_total;
   int64_t c = cap;
   if (early_exit) {
     total = total > 0 ? 1 : 0;
