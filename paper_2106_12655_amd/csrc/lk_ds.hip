@@ -558,8 +558,9 @@ __device__ __forceinline__ void make_segs(const V3<Tc>* k, Segs<Tc, R>& sg) {
 // made afresh at l and at the remainder (the same bits), so no registers hold
 // it across tiles and loops.  ALU-bound: 139 vector instructions and 5 square
 // roots a step of R = 4 before the arctangents.  The chainmail workload's
-// kernel went from 428 to 320 us, the long loops' from 33.7 to 19.0 ms (73 to
-// 123 TFLOP/s at 90 FLOP a term).
+// kernel went from 428 to 320 us (to 268 with the work queues), that of three
+// pairs of 90,000 segments from 33.7 to 18.3 ms (73 to 127 TFLOP/s at 90 FLOP a
+// term).
 // `sink` takes the sums of four steps in the compute type, then those of the
 // last steps one by one; added up in that order in FP64 they are the lane's sum.
 // EACH: it takes the steps' sums instead.
