@@ -230,8 +230,8 @@ __device__ __forceinline__ Box load_box(const double* B, int64_t cap, int64_t i)
 
 // Closed intervals on all three axes.
 __device__ __forceinline__ bool overlap(const Box& a, const Box& b) {
-  return a.lo[0] <= b.hi[0] && b.lo[0] <= a.hi[0] && a.lo[1] <= b.hi[1] && b.lo[1] <= a.hi[1] &&
-         a.lo[2] <= b.hi[2] && b.lo[2] <= a.hi[2];
+  return (a.lo[0] <= b.hi[0]) & (b.lo[0] <= a.hi[0]) & (a.lo[1] <= b.hi[1]) &
+         (b.lo[1] <= a.hi[1]) & (a.lo[2] <= b.hi[2]) & (b.lo[2] <= a.hi[2]);
 }
 
 __device__ __forceinline__ Box shfl_box(const Box& b, int src) {
@@ -445,30 +445,19 @@ __global__ __launch_bounds__(kThreads) void dz_items_apply_k(DzArgs A) {
   }
 }
 
-__device__ __forceinline__ double readlane_d(double x, int l) {
-  const int64_t v = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_readlane((int)(v & 0xffffffff), l);
-  const int hi = __builtin_amdgcn_readlane((int)(v >> 32), l);
-  return __longlong_as_double(((int64_t)hi << 32) | (uint32_t)lo);
-}
-
-__device__ __forceinline__ Box readlane_box(const Box& b, int l) {
-  Box r;
-#pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    r.lo[q] = readlane_d(b.lo[q], l);
-    r.hi[q] = readlane_d(b.hi[q], l);
-  }
-  return r;
-}
-
 // One wavefront per (pair, group of a): lane t holds piece t of the group;
 // the groups of b whose boxes overlap the group's box are visited in turn,
-// and inside them only the pieces of b whose boxes overlap it, each broadcast
-// from its lane.  A wavefront takes a contiguous run of items, so it finds
-// its first pair by one search and then steps through the prefix.
+// and inside them only the pieces of b whose boxes overlap it, each read from
+// LDS by all lanes at once.  A wavefront takes a contiguous run of items, so it
+// finds its first pair by one search and then steps through the prefix.
+// Bound by the issue of these steps (431,000 in the first pass of 2,000 yarns) and
+// the loads before them.  Broadcast by twelve v_readlane a step, in the place of
+// three LDS reads, and with comparisons that left out later loads, the four passes
+// took 190 us of a call of 510, now 142 of 463.  (Four waves an item: 607.)
 __global__ __launch_bounds__(kThreads) void dz_test_k(DzArgs A) {
+  __shared__ __align__(16) Box boxes[kThreads / 64][64];
   const int lane = threadIdx.x & 63;
+  Box* const mine = boxes[threadIdx.x >> 6];  // of this wave
   const int64_t wave = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 6;
   const int64_t nwaves = ((int64_t)gridDim.x * kThreads) >> 6;
   const int64_t P = A.n_pairs;
@@ -493,7 +482,7 @@ __global__ __launch_bounds__(kThreads) void dz_test_k(DzArgs A) {
     bool ma = false;
     for (int64_t c0 = 0; c0 < ngb; c0 += 64) {
       const int64_t gb = c0 + lane;
-      const bool gok = gb < ngb && overlap(load_box(A.gbox, A.cap_g, sb0 + gb), gA);
+      const bool gok = (gb < ngb) & overlap(load_box(A.gbox, A.cap_g, sb0 + (gb < ngb ? gb : 0)), gA);
       uint64_t gm = __ballot(gok);
       while (gm) {
         const int k = __builtin_ctzll(gm);
@@ -501,16 +490,19 @@ __global__ __launch_bounds__(kThreads) void dz_test_k(DzArgs A) {
         const int64_t ub0 = ub_begin + (c0 + k) * kDzGroup;
         const bool has_b = ub0 + lane < ub_end;
         const Box pb = has_b ? load_box(A.pbox, A.cap_u, ub0 + lane) : empty_box();
-        uint64_t bm = __ballot(has_b && overlap(pb, gA));
+        uint64_t bm = __ballot(has_b & overlap(pb, gA));
+        mine[lane] = pb;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         uint64_t hit = 0;  // b pieces that some a piece overlaps
         while (bm) {
           const int kk = __builtin_ctzll(bm);
           bm &= bm - 1;
-          const Box bk = readlane_box(pb, kk);
-          const bool ov = has_a && overlap(pa, bk);
+          const Box bk = mine[kk];
+          const bool ov = has_a & overlap(pa, bk);
           ma |= ov;
           if (__ballot(ov) != 0) hit |= 1ull << kk;
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         if ((hit >> lane) & 1ull) A.mark[ub0 + lane] = 1u;
       }
     }
