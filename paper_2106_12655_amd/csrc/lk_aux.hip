@@ -1106,7 +1106,11 @@ struct PrepPieces {
   }
 };
 
+// In head_flags: the piece's share of the offsets decreases somewhere.
+constexpr uint32_t kPieceDecreases = 1u << 31;
+
 // The first loop that starts at vertex x or later (off[0] = 0), found by a wavefront.
+// Whatever the offsets hold, it ends and returns 0 .. L.
 __device__ int32_t first_loop_from(const int64_t* off, int32_t L, int64_t x, int lane) {
   int32_t lo = 0, hi = L;  // starts below lo are before x, those from hi on are not
   while (lo < hi) {
@@ -1122,12 +1126,14 @@ __device__ int32_t first_loop_from(const int64_t* off, int32_t L, int64_t x, int
   return lo;
 }
 
-// Vertices a .. b - 1 of loop l (positions from the loop's first): flags and
-// shortest squared segment in every lane, the lane's sum of coordinates returned.
+// Vertices a .. b - 1 of loop l (positions from the loop's first, a >= 0; none
+// beyond its last): flags and shortest squared segment in every lane, the lane's
+// sum of coordinates returned.
 template <typename Tin>
 __device__ double scan_part(const Tin* X, const int64_t* off, int32_t l, int64_t a, int64_t b,
                             int lane, uint32_t* flags, double* shortest) {
   const int64_t o = off[l], n = off[l + 1] - o;
+  if (b > n) b = n;
   uint32_t f = 0u;
   double s = 0.0, mn = INFINITY;
 #pragma unroll 4
@@ -1149,22 +1155,37 @@ __device__ double scan_part(const Tin* X, const int64_t* off, int32_t l, int64_t
   return s;
 }
 
+// Offsets that decrease make a loop of negative size, which is invalid by itself,
+// but then the loops' starts are not sorted and pieces miss some of their
+// vertices.  So each piece looks through an equal share of the offsets, and where
+// one finds a decrease the workgroup that ends last scans loop by loop.  Until
+// then every access stays in range: a piece leaves out what does not start where
+// sorted offsets would have it.
 template <typename Tin>
 __device__ void scan_piece(const Tin* X, const int64_t* off, int32_t L, int64_t V, int32_t k,
                            int lane, uint32_t* lf, double* minseg2, const PrepPieces& P) {
-  const int64_t len = (V + kPrepPieces - 1) / kPrepPieces, o0 = off[0];
+  const int64_t share = ((int64_t)L + kPrepPieces - 1) / kPrepPieces;
+  const int64_t end = (k + 1) * share < L ? (k + 1) * share : L;
+  bool decreases = false;
+  for (int64_t l = k * share + lane; l < end; l += 64) decreases |= off[l + 1] < off[l];
+  if (__any(decreases)) {
+    if (lane == 0) P.head_flags[k] = kPieceDecreases;
+    return;
+  }
+  const int64_t len = V > 0 ? (V + kPrepPieces - 1) / kPrepPieces : 1, o0 = off[0];
   const int64_t s = k * len, e = s + len < V ? s + len : V;
+  const bool last = k == kPrepPieces - 1;
   const int32_t l0 = first_loop_from(off, L, s, lane);
-  const int32_t l1 = k == kPrepPieces - 1 ? L : first_loop_from(off, L, s + len, lane);
+  const int32_t l1 = last ? L : first_loop_from(off, L, s + len, lane);
   double sum = 0.0, mn = INFINITY;
   uint32_t f = 0u;
-  const int64_t end0 = off[l0] - o0;  // of the loop before l0
-  const bool head = l0 > 0 && end0 > s;
   int32_t owner = -1;
-  if (head) {
-    const int64_t o = off[l0 - 1] - o0;
-    owner = (int32_t)(o / len);
-    sum += scan_part(X, off, l0 - 1, s - o, (end0 < e ? end0 : e) - o, lane, &f, &mn);
+  if (l0 > 0) {
+    const int64_t o = off[l0 - 1] - o0, end0 = off[l0] - o0;  // of the loop before l0
+    if (0 <= o && o < s && end0 > s) {
+      owner = (int32_t)(o / len);  // below k
+      sum += scan_part(X, off, l0 - 1, s - o, (end0 < e ? end0 : e) - o, lane, &f, &mn);
+    }
   }
   if (lane == 0) {
     P.head_owner[k] = owner;
@@ -1176,6 +1197,7 @@ __device__ void scan_piece(const Tin* X, const int64_t* off, int32_t L, int64_t 
   mn = INFINITY;
   for (int32_t l = l0; l < l1; ++l) {
     const int64_t o = off[l] - o0, n = off[l + 1] - off[l];
+    if (o < s || (o >= s + len && !last)) break;
     const bool on = o + n > e;  // the last of them
     sum += scan_part(X, off, l, 0, on ? e - o : n, lane, &f, &mn);
     if (n < 3) f |= kFlagBadloop;
@@ -1193,6 +1215,14 @@ __device__ void scan_piece(const Tin* X, const int64_t* off, int32_t L, int64_t 
     P.tail_min[k] = mn;
     P.xi[k] = sum;
   }
+}
+
+// Whether a piece found offsets that decrease (the same in every thread of the one
+// workgroup that calls it).
+__device__ bool pieces_decrease(const PrepPieces& P) {
+  bool d = false;
+  for (int k = threadIdx.x; k < kPrepPieces; k += 1024) d |= (P.head_flags[k] & kPieceDecreases) != 0u;
+  return __syncthreads_or(d);
 }
 
 // The parts of loops that several pieces scanned, one workgroup; returns the
@@ -1255,7 +1285,7 @@ __global__ __launch_bounds__(1024) void prep_plan_k(const Tin* X, PlanArgs A, in
     *zero_mismatch = 0ull;
     *zero_stop = 0;
   }
-  if (alone) {
+  if (alone || pieces_decrease(P)) {
     const int sub = threadIdx.x & 15, group = threadIdx.x >> 4;
     for (int64_t l = group; l < L; l += 64)
       s += scan_loop<Tin, 16>(X, A.off, l, sub, lf, minseg2);
