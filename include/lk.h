@@ -196,10 +196,11 @@ lk_status lk_direct_sum_check(lk_ctx* ctx, const void* xyz, int dtype,
  *     LK_ECAPACITY and enqueue nothing.  Other modes return LK_EINVAL.
  *   - flags may be NULL (the flags then live in the static array).
  *   - Every call on one device shares that device's array, which keeps the
- *     last call's contents (each call initialises what it reads): calls that
+ *     last call's contents (each call initialises what it reads, but for a
+ *     counter of workgroups that is 0 again after every call): calls that
  *     overlap on one device -- on different streams, from any context or
- *     thread -- race and give undefined results.  Serialise them (one stream,
- *     or events).
+ *     thread -- race and give undefined results; calls after those do not
+ *     suffer from it.  Serialise them (one stream, or events).
  *   - lk_get_stats afterwards reports the configuration used but no refit
  *     count.
  * Arguments, layout, ownership and errors are otherwise those of

@@ -1273,12 +1273,13 @@ __global__ __launch_bounds__(1024) void prep_plan_k(const Tin* X, PlanArgs A, in
     __syncthreads();
     if (threadIdx.x == 0) {
       __threadfence();  // the workgroup's pieces before its ticket
-      order = atomicAdd(P.ticket, 1u);
+      // wraps to 0 with the last workgroup: after every whole number of launches
+      // the ticket is 0, also after launches that overlapped against the rules
+      order = atomicInc(P.ticket, gridDim.x - 1);
     }
     __syncthreads();
     if (order != gridDim.x - 1) return;
     __threadfence();  // every workgroup's pieces
-    if (threadIdx.x == 0) *P.ticket = 0u;  // for the next launch
   }
   if (threadIdx.x < 2) S.counts[threadIdx.x] = 0;
   if (threadIdx.x == 0 && zero_mismatch) {

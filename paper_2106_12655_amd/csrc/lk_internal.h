@@ -377,7 +377,8 @@ hipError_t launch_finalize_split(const Sched& s, const unsigned long long* acc, 
 // schedule counts and the refit count that follows them in memory.
 hipError_t launch_sched(const Sched& s, int32_t* zero_counts_next, hipStream_t st);
 // prep, plan (main pass) and sched as one launch, for calls with few pairs.
-// pieces: kPrepPieceBytes of scratch, zero before the first launch that uses it.
+// pieces: kPrepPieceBytes of scratch, zero before the first launch that uses it
+// (every launch leaves its ticket at 0).
 constexpr int kPrepGroups = 128, kPrepPieces = 16 * kPrepGroups;
 constexpr size_t kPrepPieceBytes = 256 + (size_t)kPrepPieces * 40;
 hipError_t launch_prep_plan(const void* xyz, bool in_f64, const PlanArgs& a, int32_t n_loops,
