@@ -375,7 +375,9 @@ __device__ __forceinline__ T full_angles(const T (&X)[R], const T (&Y)[R]) {
 
 // The tangent t = Y / X of a term, by the same operations as the full-range
 // arctangent takes where 0 < X and |Y| <= X (its octant reduction is then the
-// identity).
+// identity).  That holds for t below SmallAngle::octant, which is below 1 by more
+// than a reciprocal that is off by its last place can move t: an |Y| just above X
+// can give a t just below 1.
 template <int R>
 __device__ __forceinline__ void tangents(const float (&X)[R], const float (&Y)[R], float (&t)[R]) {
   float i[R];
@@ -415,7 +417,8 @@ template <>
 struct SmallAngle<float> {
   static constexpr int kFull = LK_ATAN_DEG;
   static constexpr int D[2] = {0, 4};
-  static constexpr float lim[2] = {2.9e-4f, 0.015625f}, one = 1.0f;
+  static constexpr float lim[2] = {2.9e-4f, 0.015625f};
+  static constexpr float octant = 0.5f;  // (of the values that an instruction holds)
   float lo = INFINITY, worst = 0.0f;
   __device__ __forceinline__ void add(float x, float t) {
     lo = fminf(lo, x);
@@ -438,7 +441,8 @@ template <>
 struct SmallAngle<double> {
   static constexpr int kFull = LK_ATAN_DEG64;
   static constexpr int D[2] = {4, 7};
-  static constexpr uint32_t lim[2] = {0x3f500000u, 0x3f900000u}, one = 0x3ff00000u;  // 2^-10, 2^-6
+  static constexpr uint32_t lim[2] = {0x3f500000u, 0x3f900000u};  // 2^-10, 2^-6
+  static constexpr uint32_t octant = 0x3fefffffu;  // 1 - 2^-21
   int32_t lo = 0x7fffffff;
   uint32_t worst = 0u;
   __device__ __forceinline__ void add(double x, double t) {
@@ -463,7 +467,7 @@ struct SmallAngle<double> {
 // arctangent that serves all its lanes; every choice gives the same value, so
 // a lane's sum does not depend on what shares its wave.  Vector instructions
 // a term after X and Y, tangent and tests included: 4 (all below 2.9e-4), 10
-// (2^-6), 14 (1, the octant reduction left out) and 26, against 22 for the
+// (2^-6), 14 (below 1/2, FP64 1: the octant reduction left out) and 26, against 22 for the
 // full form alone; FP64 20, 23, 35 and 55 against 38.
 template <typename T, int N, int R>
 __device__ __forceinline__ T sum_small(const T (&t)[R]) {
@@ -485,7 +489,7 @@ __device__ __forceinline__ T step_angles(const T (&X)[R], const T (&Y)[R]) {
     for (int r = 0; r < R; ++r) a.add(X[r], t[r]);
     if (!__any(!a.below(A::lim[0]))) return sum_small<T, A::D[0], R>(t);
     if (!__any(!a.below(A::lim[1]))) return sum_small<T, A::D[1], R>(t);
-    if (!__any(!a.below(A::one))) return sum_small<T, A::kFull, R>(t);
+    if (!__any(!a.below(A::octant))) return sum_small<T, A::kFull, R>(t);
     return full_angles<T, AT, R>(X, Y);
   }
 }
