@@ -158,10 +158,11 @@ __device__ __forceinline__ void sqrt_n(const double (&x)[N], double (&y)[N]) {
 
 // Own FP32 arctangent: octant reduction to t = min/max in [0, 1], then
 // atan(t) = t q(t^2) with q the Remez minimax polynomial of atan_poly.h.
-// (0, 0) gives NaN on purpose: it only arises for touching segments.
-__device__ __forceinline__ float atan2_minimax(float y, float x) {
+// (0, 0) gives NaN on purpose: it only arises for touching segments.  inv: the
+// hardware reciprocal of max(|x|, |y|).
+__device__ __forceinline__ float atan2_minimax(float y, float x, float inv) {
   const float ax = fabsf(x), ay = fabsf(y);
-  const float t = fminf(ax, ay) * __builtin_amdgcn_rcpf(fmaxf(ax, ay));
+  const float t = fminf(ax, ay) * inv;
   const float s = t * t;
   float q = kAtanQ[LK_ATAN_DEG];
 #pragma unroll
@@ -210,7 +211,7 @@ __device__ __forceinline__ double angle<double, 1>(double y, double x) {
 }
 template <>
 __device__ __forceinline__ float angle<float, 2>(float y, float x) {
-  return atan2_minimax(y, x);
+  return atan2_minimax(y, x, __builtin_amdgcn_rcpf(fmaxf(fabsf(x), fabsf(y))));
 }
 template <>
 __device__ __forceinline__ double angle<double, 2>(double y, double x) {
@@ -365,11 +366,21 @@ __device__ __forceinline__ void walk_xy(Walk<T, R>& w, const V3<T>& l1, const Se
 }
 
 // 2 pi times the sum of the step's R terms, by the arctangent of the full range.
-template <typename T, int AT, int R>
+// RUN: in a run of such steps, where FP32's reciprocals are a block (rcp_n).
+template <typename T, int AT, int R, bool RUN = false>
 __device__ __forceinline__ T full_angles(const T (&X)[R], const T (&Y)[R]) {
   T sum = 0;
+  if constexpr (RUN && sizeof(T) == 4 && AT == 2) {
+    T mx[R], inv[R];
 #pragma unroll
-  for (int r = 0; r < R; ++r) sum += angle<T, AT>(Y[r], X[r]);
+    for (int r = 0; r < R; ++r) mx[r] = fmaxf(fabsf(X[r]), fabsf(Y[r]));
+    rcp_n<R>(mx, inv);
+#pragma unroll
+    for (int r = 0; r < R; ++r) sum += atan2_minimax(Y[r], X[r], inv[r]);
+  } else {
+#pragma unroll
+    for (int r = 0; r < R; ++r) sum += angle<T, AT>(Y[r], X[r]);
+  }
   return sum;
 }
 
@@ -467,8 +478,9 @@ struct SmallAngle<double> {
 // arctangent that serves all its lanes; every choice gives the same value, so
 // a lane's sum does not depend on what shares its wave.  Vector instructions
 // a term after X and Y, tangent and tests included: 4 (all below 2.9e-4), 10
-// (2^-6), 14 (below 1/2, FP64 1: the octant reduction left out) and 26, against 22 for the
-// full form alone; FP64 20, 23, 35 and 55 against 38.
+// (2^-6), 14 (below 1/2, FP64 1: the octant reduction left out) and 26, against 22
+// for the full form alone; FP64 20, 23, 35 and 55 against 38.  `full` counts the
+// steps that took the full form, for the walk to leave the tests out (kFullRun).
 template <typename T, int N, int R>
 __device__ __forceinline__ T sum_small(const T (&t)[R]) {
   T sum = 0;
@@ -477,7 +489,7 @@ __device__ __forceinline__ T sum_small(const T (&t)[R]) {
   return sum;
 }
 template <typename T, int AT, int R>
-__device__ __forceinline__ T step_angles(const T (&X)[R], const T (&Y)[R]) {
+__device__ __forceinline__ T step_angles(const T (&X)[R], const T (&Y)[R], int& full) {
   using A = SmallAngle<T>;
   if constexpr (AT == 1) {
     return full_angles<T, AT, R>(X, Y);
@@ -490,6 +502,7 @@ __device__ __forceinline__ T step_angles(const T (&X)[R], const T (&Y)[R]) {
     if (!__any(!a.below(A::lim[0]))) return sum_small<T, A::D[0], R>(t);
     if (!__any(!a.below(A::lim[1]))) return sum_small<T, A::D[1], R>(t);
     if (!__any(!a.below(A::octant))) return sum_small<T, A::kFull, R>(t);
+    ++full;
     return full_angles<T, AT, R>(X, Y);
   }
 }
@@ -565,9 +578,17 @@ __device__ __forceinline__ void make_segs(const V3<Tc>* k, Segs<Tc, R>& sg) {
 // kernel went from 428 to 320 us (to 268 with the work queues), that of three
 // pairs of 90,000 segments from 33.7 to 18.3 ms (73 to 127 TFLOP/s at 90 FLOP a
 // term).
+// After four steps that all took the full arctangent, the next kFullRun groups of
+// four take it without a test: where all angles are large (random polygons) the
+// tests cost a fifth of an FP64 walk.  1,770 pairs of 1,000 random segments took
+// 6,520 us in FP64 and 2,930 mixed without such runs, now 5,510 and 2,580 (5,430
+// and 2,500 with the full form alone); smooth curves never get there.  A branch in
+// each step, in the place of one around groups, cost those 3-11%.  FP32 runs are
+// not unrolled: its registers are all in use.
 // `sink` takes the sums of four steps in the compute type, then those of the
 // last steps one by one; added up in that order in FP64 they are the lane's sum.
 // EACH: it takes the steps' sums instead.
+constexpr int kFullRun = 16;
 template <typename Tc, int AT, int R, bool EACH = false, typename Sink>
 __device__ __forceinline__ void walk(const Vtx<Tc>* l, const Vtx<Tc>* le, bool first,
                                      const Segs<Tc, R>& sg, const Sink& sink) {
@@ -576,21 +597,46 @@ __device__ __forceinline__ void walk(const Vtx<Tc>* l, const Vtx<Tc>* le, bool f
     walk_init(wk, V3<Tc>{l[0].x, l[0].y, l[0].z}, sg, first);
     first = false;
     V3<Tc> vn{l[1].x, l[1].y, l[1].z};
-    for (; l + 4 <= le; l += 4) {
-      Tc s4 = 0;
+    // one step to vn; `next` is the vertex after it
+    const auto step = [&](const Vtx<Tc>* next, const auto& angles,
+                          Tc& s4) __attribute__((always_inline)) {
+      const V3<Tc> v1 = vn;
+      Tc X[R], Y[R];
+      vn = {next->x, next->y, next->z};
+      walk_xy(wk, v1, sg, X, Y);
+      if constexpr (EACH)
+        sink(angles(X, Y));
+      else
+        s4 += angles(X, Y);
+    };
+    using Args = const Tc(&)[R];
+    do {
+      int full;
+      do {
+        Tc s4 = 0;
+        full = 0;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const V3<Tc> v1 = vn;
-        Tc X[R], Y[R];
-        vn = {l[q + 2].x, l[q + 2].y, l[q + 2].z};  // the next step's
-        walk_xy(wk, v1, sg, X, Y);
-        if constexpr (EACH)
-          sink(step_angles<Tc, AT, R>(X, Y));
-        else
-          s4 += step_angles<Tc, AT, R>(X, Y);
+        for (int q = 0; q < 4; ++q)
+          step(l + q + 2, [&](Args X, Args Y) { return step_angles<Tc, AT, R>(X, Y, full); }, s4);
+        if constexpr (!EACH) sink(s4);
+        l += 4;
+      } while (full < 4 && l + 4 <= le);
+      if (__builtin_expect(full == 4, 0)) {
+        for (int k = 0; k < kFullRun && l + 4 <= le; ++k) {
+          const auto angles = [](Args X, Args Y) { return full_angles<Tc, AT, R, true>(X, Y); };
+          Tc s4 = 0;
+          if constexpr (sizeof(Tc) == 8) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) step(l + q + 2, angles, s4);
+            l += 4;
+          } else {
+#pragma unroll 1
+            for (int q = 0; q < 4; ++q) step(++l + 1, angles, s4);
+          }
+          if constexpr (!EACH) sink(s4);
+        }
       }
-      if constexpr (!EACH) sink(s4);
-    }
+    } while (l + 4 <= le);
   }
   if (l < le) {
     Walk<Tc, R> wk;
@@ -599,7 +645,8 @@ __device__ __forceinline__ void walk(const Vtx<Tc>* l, const Vtx<Tc>* le, bool f
       ++l;
       Tc X[R], Y[R];
       walk_xy(wk, V3<Tc>{l[0].x, l[0].y, l[0].z}, sg, X, Y);
-      sink(step_angles<Tc, AT, R>(X, Y));
+      int full = 0;
+      sink(step_angles<Tc, AT, R>(X, Y, full));
     } while (l < le);
   }
 }
@@ -875,7 +922,7 @@ __device__ __forceinline__ void finish_item(double acc, int32_t p, int lane, con
 // While transcendentals left the waves out of step (sqrt_n), the placement moved
 // a call's time by 7-10%; now offsets of 0-16 bytes give 349.3-350.4 us on the
 // chainmail workload.  A CPU test checks the placements.
-constexpr int kPadPacked = 3, kPadWhole = 1, kPadBig = 1;
+constexpr int kPadPacked = 4, kPadWhole = 1, kPadBig = 5;
 template <typename Tin, typename Tc, int AT, int R, bool PK, int N>
 __device__ __forceinline__ void place_code() {
   if constexpr (PK && sizeof(Tin) == 4 && sizeof(Tc) == 4 && AT == 2 && R == 4 && N > 0)
