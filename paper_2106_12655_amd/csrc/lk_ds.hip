@@ -1130,7 +1130,12 @@ __global__ __launch_bounds__(kWave, (waves_per_simd<Tc, AT, R>())) void ds_persi
 // A small pair is summed by the team's first wave, all 64 lanes (each walks less
 // of loop A than in a packed round).  ALU-bound as ds_persistent is.
 // Eight waves (FP64: four, which its registers let a compute unit hold two teams
-// of) and U = 64 share the default tile; the LDS of two teams is 2 x 47 KB.
+// of) and U = 64 share the default tile; the LDS of two teams is 2 x 47 KB.  An
+// FP64 tile of fewer steps is shared out in shorter pieces: with 64 the last waves
+// of a team had none, and 512 pairs of 130 segments took 140 us, 107 so (an item
+// per wave 108; 400 of 200 segments 132, 115, 138).  FP32 keeps pieces of 64: it
+// starts a walk for each, which costs where the chip is full (neighbours of 100
+// yarns 2,157 us, in shorter pieces 2,240).
 // Against an item per wave, us per call on one MI355X: 276 pairs of 5 to 5,000
 // segments 1,610 -> 546, neighbours of 100 yarns of up to 16,384 segments 3,330 ->
 // 2,460, of 60 yarns in FP64 3,930 -> 2,560, three pairs of 90,000 segments 21,290
@@ -1155,7 +1160,7 @@ __global__ __launch_bounds__(kWave * kTeam<Tc>, (sizeof(Tc) == 4 ? 4 : 2)) void 
   Vtx<Tc>* lds = reinterpret_cast<Vtx<Tc>*>(lds_raw);
   const int n_vtx = A.tile + 2 > kSmallA + 1 ? A.tile + 2 : kSmallA + 1;
   Tc* slots = reinterpret_cast<Tc*>(lds + n_vtx);
-  const int U = uniform((int32_t)team_piece<Tc>(A.tile)), E = U / 4 + 3;
+  const int U_max = uniform((int32_t)team_piece<Tc>(A.tile)), E = U_max / 4 + 3;
   const int wv = uniform((int32_t)(threadIdx.x >> 6));
   // The thread's index, read again wherever it is used: what comes from it,
   // kept across the walk, would cost FP32 registers that it has not got.
@@ -1209,8 +1214,20 @@ __global__ __launch_bounds__(kWave * kTeam<Tc>, (sizeof(Tc) == 4 ? 4 : 2)) void 
       Segs<Tc, R> sg;
       make_segs<Tc, R>(kv, sg);
       double acc = 0.0;  // the first wave's
+      int per_lane = 0;  // FP64: a lane's steps at most
+      if constexpr (sizeof(Tc) == 8) {
+        const int n_slots = uniform((L.nbh + R - 1) / R);
+        const int n_groups = n_slots <= kWave ? kWave / n_slots : 1;
+        per_lane = (uniform(L.nah) + n_groups - 1) / n_groups;
+      }
       for (int t0 = 0; t0 < L.nah; t0 += A.tile) {
         const int tl = (L.nah - t0) < A.tile ? (L.nah - t0) : A.tile;
+        int steps = tl, U = U_max;
+        if constexpr (sizeof(Tc) == 8) {
+          if (per_lane < steps) steps = per_lane;
+          const int share = ((steps + kTeam<Tc> - 1) / kTeam<Tc> + 3) & ~3;
+          if (share < U) U = share;
+        }
         for (int v = tid(); v <= tl; v += kWave * kTeam<Tc>) {
           unsigned idx = (unsigned)L.a0 + (unsigned)t0 + (unsigned)v;
           if (idx >= (unsigned)r.na) idx -= (unsigned)r.na;  // closing vertex of the loop
@@ -1218,7 +1235,7 @@ __global__ __launch_bounds__(kWave * kTeam<Tc>, (sizeof(Tc) == 4 ? 4 : 2)) void 
           lds[v] = Vtx<Tc>{x.x, x.y, x.z, (Tc)0};
         }
         __syncthreads();  // the tile is there, and the slots are read
-        for (int u0 = 0; u0 * U < tl; u0 += kTeam<Tc>) {
+        for (int u0 = 0; u0 * U < steps; u0 += kTeam<Tc>) {
           if (u0 > 0) __syncthreads();  // the slots are read
           const int ln = tid() & 63;
           const Layout M = layout<R>(r, local, A.chunk, ln);
