@@ -1127,8 +1127,11 @@ __global__ __launch_bounds__(kWave, (waves_per_simd<Tc, AT, R>())) void ds_persi
 // while the others stage the next tile.  The pieces start every U steps (a
 // multiple of four) from where the lane's walk of the tile starts, so the groups
 // of four are those of ds_persistent, and a big pair's value is the same in both.
-// A small pair is summed by the team's first wave, all 64 lanes (each walks less
-// of loop A than in a packed round).  ALU-bound as ds_persistent is.
+// A small pair is summed by one wave, all 64 lanes (each walks less of loop A than
+// in a packed round), a work index taking up to kTeam of them: one in the main
+// pass, which spreads them, kTeam in the refit pass, whose teams are few (with one
+// a team 500 pairs of 100 segments that all need a refit took 370 us a call, now
+// 148; 151 with an item per wave).  ALU-bound as ds_persistent is.
 // Eight waves (FP64: four, which its registers let a compute unit hold two teams
 // of) and U = 64 share the default tile; the LDS of two teams is 2 x 47 KB.  An
 // FP64 tile of fewer steps is shared out in shorter pieces: with 64 the last waves
@@ -1172,7 +1175,10 @@ __global__ __launch_bounds__(kWave * kTeam<Tc>, (sizeof(Tc) == 4 ? 4 : 2)) void 
   const Tin* X = static_cast<const Tin*>(A.xyz);
   const int64_t big_total = uniform(*A.s.big_total);
   const int64_t n_big = uniform(A.s.counts[1]);
-  const int64_t total = big_total + uniform(A.s.counts[0]);  // small pairs one by one
+  const int64_t n_small = uniform(A.s.counts[0]);
+  // small pairs a work index (FP32 teams run no refits)
+  const int per = sizeof(Tc) == 4 ? 1 : A.batch < kTeam<Tc> ? A.batch : kTeam<Tc>;
+  const int64_t total = big_total + (n_small + per - 1) / per;
 
   // work indices as in ds_persistent, one ahead, in the first thread
   int64_t w = blockIdx.x;
@@ -1266,10 +1272,11 @@ __global__ __launch_bounds__(kWave * kTeam<Tc>, (sizeof(Tc) == 4 ? 4 : 2)) void 
         }
       }
       if (wv == 0) finish_item<AT>(acc, r.p, lane, A, r.items == 1, fpre);
-    } else if (wv == 0) {
-      // one small pair on the first wave (one wave: LDS accesses stay in order)
+    } else if (wv < per && (w - big_total) * per + wv < n_small) {
+      // a small pair on this wave (one wave: LDS accesses stay in order)
       const int lane = tid() & 63;
-      const WorkRec cur = uniform(A.s.small[w - big_total]);
+      Vtx<Tc>* const own = per == 1 ? lds : lds + wv * (kSmallA + 1);
+      const WorkRec cur = uniform(A.s.small[(w - big_total) * per + wv]);
       const uint32_t fm = A.out.flags[cur.p];
       const Layout L = layout<R>(cur, 0, A.chunk, lane);
       Frame<Tin, Tc> F;
@@ -1279,14 +1286,14 @@ __global__ __launch_bounds__(kWave * kTeam<Tc>, (sizeof(Tc) == 4 ? 4 : 2)) void 
       load_b<Tin, Tc, R>(X, cur, L, F, kv);
       const V3<Tc> a_lo = F.load(X, cur.oa + (lane < cur.na ? lane : 0));
       const V3<Tc> a_hi = F.load(X, cur.oa + (lane + kWave < cur.na ? lane + kWave : 0));
-      if (lane <= cur.na) lds[lane] = Vtx<Tc>{a_lo.x, a_lo.y, a_lo.z, (Tc)0};
-      if (lane + kWave <= cur.na) lds[lane + kWave] = Vtx<Tc>{a_hi.x, a_hi.y, a_hi.z, (Tc)0};
+      if (lane <= cur.na) own[lane] = Vtx<Tc>{a_lo.x, a_lo.y, a_lo.z, (Tc)0};
+      if (lane + kWave <= cur.na) own[lane + kWave] = Vtx<Tc>{a_hi.x, a_hi.y, a_hi.z, (Tc)0};
       Segs<Tc, R> sg;
       make_segs<Tc, R>(kv, sg);
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       double acc = 0.0;
       if (L.active && L.js < L.je)
-        walk_tile<Tc, AT, R>(lds + L.js, lds + L.je, true, sg, acc);
+        walk_tile<Tc, AT, R>(own + L.js, own + L.je, true, sg, acc);
       finish_item<AT>(acc, cur.p, lane, A, true, fm);
     }
     if (tid() == 0) {
@@ -1436,11 +1443,14 @@ int grid_t(int tile, int n_cu, int waves_per_cu) {
   return resident(e, per_cu, 1, n_cu, waves_per_cu);
 }
 
-// The team kernel's tile, or one small pair's loop A, and the teams' slots.
+// The team kernel's tile and the waves' slots, or small pairs' loops A.
 template <typename Tc>
 size_t team_lds(int tile) {
   const int n = tile + 2 > kSmallA + 1 ? tile + 2 : kSmallA + 1;
-  return (size_t)n * sizeof(Vtx<Tc>) + (size_t)kTeam<Tc> * team_slots<Tc>(tile) * kWave * sizeof(Tc);
+  const size_t big =
+      (size_t)n * sizeof(Vtx<Tc>) + (size_t)kTeam<Tc> * team_slots<Tc>(tile) * kWave * sizeof(Tc);
+  const size_t small = (size_t)kTeam<Tc> * (kSmallA + 1) * sizeof(Vtx<Tc>);
+  return big > small ? big : small;
 }
 template <typename Tin, typename Tc, int R>
 hipError_t launch_team(const DsArgs& a, int grid, hipStream_t s) {

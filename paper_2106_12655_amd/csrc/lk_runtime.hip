@@ -524,9 +524,9 @@ lk_status enqueue_direct_sum(lk_ctx* ctx, const Ws& W, const Plan& P, const void
     B.s = make_sched(W, n_pairs, 1);
     B.tile = default_tile(true);
     B.chunk = R.chunk;
-    // refits are few and latency-bound: one pair per work index spreads them
-    // over the most waves
-    B.batch = 1;
+    // refits are few and latency-bound: one pair per wave of the pass's grid
+    // spreads them over the most waves
+    B.batch = P.crossings ? 1 : direct_sum_waves(P.in_f64, true, 0, P.segs64, P.unpacked);
     B.out = ro;
     int32_t* zero_next = P.crossings ? W.at<int32_t>(kMetaCountsRefit2) : nullptr;
     if (P.bh) {
@@ -557,6 +557,7 @@ lk_status enqueue_direct_sum(lk_ctx* ctx, const Ws& W, const Plan& P, const void
       B2.cc_blk = B2.cc_sup = nullptr;
       B2.s = make_sched(W, n_pairs, 2);
       B2.chunk = R2.chunk;
+      B2.batch = direct_sum_waves(P.in_f64, true, 0, P.segs64, P.unpacked);
       B2.out = r2;
       // the FP64 crossing count's split pairs are finalised (queuing what it
       // cannot decide) in the launch that plans the direct sum of those
@@ -598,8 +599,8 @@ Plan make_plan(lk_ctx* ctx, bool in_f64, int mode, int64_t n_pairs) {
                                  ctx->n_cu, ctx->opt_waves, P.unpacked);
   P.waves = mixed ? P.grid * lk::direct_sum_waves(in_f64, false, P.atan_form, P.segs, P.unpacked)
                   : P.grid64 * lk::direct_sum_waves(in_f64, true, 0, P.segs64, P.unpacked);
-  // refits of the direct sum are rare: one wave per CU keeps the empty refit
-  // pass cheap (4.7 instead of 7.8 us on chainmail).  Barnes-Hut sends every
+  // refits of the direct sum are rare: one wave per CU (in teams: their share of
+  // teams) keeps the empty refit pass cheap (4.7 instead of 7.8 us on chainmail).  Barnes-Hut sends every
   // pair whose far-field error estimate stays too large there (hundreds of
   // big pairs on knit with adaptive beta), so its refit pass gets the whole
   // grid.
