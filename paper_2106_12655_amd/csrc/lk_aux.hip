@@ -910,14 +910,22 @@ __global__ __launch_bounds__(64 * kFillRows) void rows_count_k(const double* box
 // tiles and of its tile's earlier rows, which each workgroup adds up itself
 // (cheaper than a scan in a launch of its own).  Nothing is written unless all
 // pairs fit; the first workgroup reports the total to the host.  A row whose
-// pairs are all in its slots is sorted by counting, lane against lane; a longer
-// one is searched again, and one lane sorts it in place if the grid gave it.
+// pairs are all in its slots is sorted by counting, lane against lane.  A longer
+// one is searched again; if the grid gives it, the wave gathers up to kRowSort
+// second indices in LDS and counts for each how many are below it, and a row of
+// more is searched without the grid, which gives them in order.  (Sorted in place by
+// one lane, a search of 7,000 loops whose 64 first rows have up to 238 pairs took
+// 1,740 us, 1,024 rows of up to 1,059 141,000 us, 20,000 loops of 114 pairs a row
+// 18,600 us; now 330, 815 and 1,900.  The registers of five waves a SIMD: with four,
+// sheets of 20,000 loops took 96 us, with five 90.)
+constexpr int kRowSort = 1024;
 template <bool GRID>
-__global__ __launch_bounds__(256) void rows_fill_k(const double* box, int32_t L, RowGrid R,
+__global__ __launch_bounds__(256, 5) void rows_fill_k(const double* box, int32_t L, RowGrid R,
                                                    RowBufs B, int32_t* out, int64_t capacity,
                                                    int64_t* host_total) {
   __shared__ int64_t red[2][4];
   __shared__ int32_t row_n[kFillRows];
+  __shared__ __align__(16) int32_t gathered[GRID ? 4 : 1][GRID ? kRowSort : 4];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t base = (int64_t)blockIdx.x * kFillRows;
   const int64_t tile = base / kRowTile, n_tiles = (L + kRowTile - 1) / kRowTile;
@@ -961,9 +969,31 @@ __global__ __launch_bounds__(256) void rows_fill_k(const double* box, int32_t L,
           out[2 * (pos + rank)] = (int32_t)i;
           out[2 * (pos + rank) + 1] = j;
         }
+      } else if (GRID && n <= kRowSort && R.cell_of[i] >= 0) {
+        int32_t* const g = gathered[w];
+        int32_t to = 0;  // uniform over the wave
+        row_candidates<GRID>(box, L, i, R, [&](bool hit, int32_t j) {
+          const unsigned long long m = __ballot(hit);
+          if (hit) g[to + (int32_t)__popcll(m & below)] = j;
+          to += (int32_t)__popcll(m);
+        });
+        if (lane < 3 && n + lane < kRowSort) g[n + lane] = INT32_MAX;  // up to a multiple of four
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        for (int k = lane; k < n; k += 64) {
+          const int32_t j = g[k];
+          int32_t rank = 0;
+#pragma unroll 4
+          for (int u = 0; u < n; u += 4) {
+            const int4 v = *reinterpret_cast<const int4*>(g + u);
+            rank += (v.x < j) + (v.y < j) + (v.z < j) + (v.w < j);
+          }
+          out[2 * (pos + rank)] = (int32_t)i;
+          out[2 * (pos + rank) + 1] = j;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       } else {
         int64_t to = pos;  // uniform over the wave
-        row_candidates<GRID>(box, L, i, R, [&](bool hit, int32_t j) {
+        row_candidates<false>(box, L, i, R, [&](bool hit, int32_t j) {
           const unsigned long long m = __ballot(hit);
           if (hit) {
             const int64_t at = to + __popcll(m & below);
@@ -972,19 +1002,6 @@ __global__ __launch_bounds__(256) void rows_fill_k(const double* box, int32_t L,
           }
           to += __popcll(m);
         });
-        if (GRID && R.cell_of[i] >= 0) {
-          __threadfence_block();
-          if (lane == 0)
-            for (int64_t k = pos + 1; k < pos + n; ++k) {
-              const int32_t v = out[2 * k + 1];
-              int64_t m = k - 1;
-              while (m >= pos && out[2 * m + 1] > v) {
-                out[2 * (m + 1) + 1] = out[2 * m + 1];
-                --m;
-              }
-              out[2 * (m + 1) + 1] = v;
-            }
-        }
       }
     }
     pos += n;
