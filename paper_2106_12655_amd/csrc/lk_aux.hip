@@ -568,6 +568,11 @@ __device__ __forceinline__ void clear_tiles(unsigned long long* tiles, int32_t L
     tiles[k] = 0ull;
 }
 
+// A loop of more than kBoxNarrow vertices is left by its 16 lanes to the whole wave:
+// 10,000 loops of 32 vertices and one of a million took 15,100 us by 16 lanes,
+// 3,940 so (4,320 with a wave for every loop).  Loops of some hundred vertices are
+// better side by side: 10,000 of 2,000 take 112 us a search, by waves in turn 116.
+constexpr int64_t kBoxNarrow = 2048;
 template <typename Tin, int W>
 __global__ __launch_bounds__(256) void boxes_k(const Tin* X, const int64_t* off, int32_t L,
                                                double* box, unsigned long long* tiles) {
@@ -581,10 +586,23 @@ __global__ __launch_bounds__(256) void boxes_k(const Tin* X, const int64_t* off,
     const int64_t l = first + t * stride;
     MinMax<Tin> m;
     m.clear();
-    if (l < L)
-      for (int64_t v = off[l] + sub; v < off[l + 1]; v += W) m.add(X + 3 * v);
+    const int64_t v0 = l < L ? off[l] : 0, v1 = l < L ? off[l + 1] : 0;
+    const bool wide = W < 64 && v1 - v0 > kBoxNarrow;
+    if (!wide)
+      for (int64_t v = v0 + sub; v < v1; v += W) m.add(X + 3 * v);
     m.template reduce<W>();
-    if (l < L && sub == 0) m.store(box + 6 * l);
+    if (l < L && sub == 0 && !wide) m.store(box + 6 * l);
+    if constexpr (W < 64) {
+      for (unsigned long long left = __ballot(wide && sub == 0); left; left &= left - 1ull) {
+        const int from = __ffsll((long long)left) - 1;  // the loop's first lane
+        const int64_t a = __shfl(v0, from), b = __shfl(v1, from), to = __shfl(l, from);
+        MinMax<Tin> all;
+        all.clear();
+        for (int64_t v = a + (int)(threadIdx.x & 63); v < b; v += 64) all.add(X + 3 * v);
+        all.template reduce<64>();
+        if ((threadIdx.x & 63) == 0) all.store(box + 6 * to);
+      }
+    }
   }
 }
 
@@ -1427,7 +1445,8 @@ hipError_t launch_scan(const int64_t* counts, int64_t n, int64_t* prefix, int64_
 // A workgroup per loop below 2,048 loops (of 1,024 threads below 256, where
 // loops may be long: 100 knit rows of 8,000 vertices took 77 us with a
 // wavefront each, 14 us so), a wavefront per loop below 8,192, 16 lanes above
-// (20,000 loops of 32 vertices: 19.8 us with a wavefront each, 5.6 us so).
+// (20,000 loops of 32 vertices: 19.8 us with a wavefront each, 5.6 us so) for
+// loops of up to kBoxNarrow vertices.
 hipError_t launch_boxes(const void* xyz, bool in_f64, const int64_t* off, int32_t n_loops,
                         double* boxes, unsigned long long* tiles, hipStream_t s) {
   auto go = [&](auto* X) {
