@@ -518,7 +518,7 @@ __global__ __launch_bounds__(1024) void sched_k(Sched S, int32_t* zero_next) {
   schedule(S, zero_next);
 }
 
-// General single-workgroup exclusive scan (pair search, verification).
+// Single-workgroup exclusive scan (tiles of the pair search, verification).
 __global__ __launch_bounds__(1024) void scan_k(const int64_t* counts, int64_t n, int64_t* prefix,
                                                int64_t* host_total) {
   __shared__ int64_t wsum[16];
@@ -929,8 +929,11 @@ __global__ __launch_bounds__(64 * kFillRows) void rows_count_k(const double* box
 
 // Writes the rows, 16 per workgroup.  A row's place is the sum of the earlier
 // tiles and of its tile's earlier rows, which each workgroup adds up itself
-// (cheaper than a scan in a launch of its own).  Nothing is written unless all
-// pairs fit; the first workgroup reports the total to the host.  A row whose
+// (cheaper than a scan in a launch of its own), but for more than kRowTilesDirect
+// tiles, which a launch before scans (SCANNED): added up by every workgroup they
+// took 90 of the 150 ms of a search of 30 million loops.  (At one million 1,940 us
+// so, 1,830 scanned; at 60,000 168 and a launch more.)
+// Nothing is written unless all pairs fit; the first workgroup reports the total to the host.  A row whose
 // pairs are all in its slots is sorted by counting, lane against lane.  A longer
 // one is searched again; if the grid gives it, the wave gathers up to kRowSort
 // second indices in LDS and counts for each how many are below it, and a row of
@@ -940,7 +943,8 @@ __global__ __launch_bounds__(64 * kFillRows) void rows_count_k(const double* box
 // 18,600 us; now 330, 815 and 1,900.  The registers of five waves a SIMD: with four,
 // sheets of 20,000 loops took 96 us, with five 90.)
 constexpr int kRowSort = 1024;
-template <bool GRID>
+constexpr int64_t kRowTilesDirect = 1024;
+template <bool GRID, bool SCANNED>
 __global__ __launch_bounds__(256, 5) void rows_fill_k(const double* box, int32_t L, RowGrid R,
                                                    RowBufs B, int32_t* out, int64_t capacity,
                                                    int64_t* host_total) {
@@ -951,11 +955,12 @@ __global__ __launch_bounds__(256, 5) void rows_fill_k(const double* box, int32_t
   const int64_t base = (int64_t)blockIdx.x * kFillRows;
   const int64_t tile = base / kRowTile, n_tiles = (L + kRowTile - 1) / kRowTile;
   int64_t before = 0, total = 0;
-  for (int64_t k = threadIdx.x; k < n_tiles; k += 256) {
-    const int64_t c = (int64_t)B.tiles[k];
-    total += c;
-    if (k < tile) before += c;
-  }
+  if (!SCANNED)
+    for (int64_t k = threadIdx.x; k < n_tiles; k += 256) {
+      const int64_t c = (int64_t)B.tiles[k];
+      total += c;
+      if (k < tile) before += c;
+    }
   const int64_t r = tile * kRowTile + threadIdx.x;  // kRowTile == 256
   const int32_t c = r < L ? B.counts[r] : 0;
   if (r < base) before += c;
@@ -969,11 +974,12 @@ __global__ __launch_bounds__(256, 5) void rows_fill_k(const double* box, int32_t
     red[1][w] = total;
   }
   __syncthreads();
-  total = red[1][0] + red[1][1] + red[1][2] + red[1][3];
-  if (blockIdx.x == 0 && threadIdx.x == 0)
+  total = SCANNED ? (int64_t)B.tiles[n_tiles] : red[1][0] + red[1][1] + red[1][2] + red[1][3];
+  if (!SCANNED && blockIdx.x == 0 && threadIdx.x == 0)
     __hip_atomic_store(host_total, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   if (total > capacity) return;
   int64_t pos = red[0][0] + red[0][1] + red[0][2] + red[0][3];
+  if (SCANNED) pos += (int64_t)B.tiles[tile];
   const unsigned long long below = lane ? (~0ull >> (64 - lane)) : 0ull;
   for (int q = 0; q < kFillRows; ++q) {
     const int64_t i = base + q;
@@ -1486,14 +1492,21 @@ hipError_t launch_pair_rows(const double* boxes, int32_t n_loops, const RowGrid*
                             const RowBufs& b, int32_t* pairs_out, int64_t capacity,
                             int64_t* host_total, hipStream_t s) {
   const unsigned gf = (unsigned)(((int64_t)n_loops + kFillRows - 1) / kFillRows);
-  if (grid) {
-    rows_count_k<true><<<gf, 64 * kFillRows, 0, s>>>(boxes, n_loops, *grid, b);
-    rows_fill_k<true><<<gf, 256, 0, s>>>(boxes, n_loops, *grid, b, pairs_out, capacity, host_total);
-  } else {
-    rows_count_k<false><<<gf, 64 * kFillRows, 0, s>>>(boxes, n_loops, RowGrid{}, b);
-    rows_fill_k<false><<<gf, 256, 0, s>>>(boxes, n_loops, RowGrid{}, b, pairs_out, capacity,
-                                          host_total);
-  }
+  const int64_t n_tiles = ((int64_t)n_loops + kRowTile - 1) / kRowTile;
+  const RowGrid g = grid ? *grid : RowGrid{};
+  auto go = [&](auto with_grid, auto scanned) {
+    constexpr bool G = decltype(with_grid)::value, S = decltype(scanned)::value;
+    rows_count_k<G><<<gf, 64 * kFillRows, 0, s>>>(boxes, n_loops, g, b);
+    if (S)
+      scan_k<<<1, 1024, 0, s>>>((const int64_t*)b.tiles, n_tiles, (int64_t*)b.tiles, host_total);
+    rows_fill_k<G, S><<<gf, 256, 0, s>>>(boxes, n_loops, g, b, pairs_out, capacity, host_total);
+  };
+  const std::true_type yes;
+  const std::false_type no;
+  if (n_tiles > kRowTilesDirect)
+    grid ? go(yes, yes) : go(no, yes);
+  else
+    grid ? go(yes, no) : go(no, no);
   return hipGetLastError();
 }
 

@@ -408,7 +408,7 @@ hipError_t launch_boxes(const void* xyz, bool in_f64, const int64_t* off, int32_
 constexpr int kRowTile = 256, kRowSlots = 32, kFillRows = 16;
 struct RowBufs {
   int32_t* counts;            // [L]
-  unsigned long long* tiles;  // [ceil(L / kRowTile)]
+  unsigned long long* tiles;  // [ceil(L / kRowTile) + 1]: the last for a scan's total
   int32_t* slots;             // [L][kRowSlots]
 };
 

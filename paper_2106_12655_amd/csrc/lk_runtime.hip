@@ -740,14 +740,14 @@ lk_status ensure_rows(lk_ctx* ctx, int32_t n_loops) {
   lk_status st;
   if ((st = ensure_host(ctx)) != LK_OK) return st;
   if ((st = ensure(ctx, ctx->boxes, 48 * L)) != LK_OK) return st;
-  return ensure(ctx, ctx->pls_rows, 8 * (L / lk::kRowTile + 1) + 4 * L * (1 + lk::kRowSlots));
+  return ensure(ctx, ctx->pls_rows, 8 * (L / lk::kRowTile + 2) + 4 * L * (1 + lk::kRowSlots));
 }
 
 lk::RowBufs row_bufs(lk_ctx* ctx, int32_t n_loops) {
   const size_t L = (size_t)n_loops;
   lk::RowBufs b;
   b.tiles = (unsigned long long*)ctx->pls_rows.p;
-  b.counts = (int32_t*)((char*)ctx->pls_rows.p + 8 * (L / lk::kRowTile + 1));
+  b.counts = (int32_t*)((char*)ctx->pls_rows.p + 8 * (L / lk::kRowTile + 2));
   b.slots = b.counts + L;
   return b;
 }
@@ -1765,7 +1765,7 @@ int64_t ctx_workspace_need(int mode, int32_t n_loops, int64_t n_pairs, int64_t n
              3.0 * sizeof(WorkRec) * P + 8.0 * (P + 1) + (double)kMetaBytes + 16.0 * P +
              8.0 * P + 4.0 * P;
   // the pair search: boxes, rows, and the grid
-  b += 48.0 * L + 4.0 * L * (1 + kRowSlots) + 8.0 * (L / kRowTile + 1) +
+  b += 48.0 * L + 4.0 * L * (1 + kRowSlots) + 8.0 * (L / kRowTile + 2) +
        (n_loops >= kGridLoops ? (double)grid_bytes(n_loops) : 0.0);
   // verification's flags and prefix over current + expected pairs
   b += 16.0 * (double)(n_verify + 1);
