@@ -287,7 +287,9 @@ enum {
                                      synchronises the device and clears the ring. */
   LK_OPT_TILE_A = 4,              /* FP32 LDS tile of loop A in vertices (0 = tuned) */
   LK_OPT_CHUNK_A = 5,             /* vertices of A per work item (0 = tuned) */
-  LK_OPT_WAVES_PER_CU = 6,        /* persistent waves per compute unit (0 = occupancy) */
+  LK_OPT_WAVES_PER_CU = 6,        /* persistent waves per compute unit (0 = occupancy); in
+                                     calls with few pairs, whose workgroups are 8 waves
+                                     (FP64: 4), on average over the units */
   LK_OPT_ATAN = 7,                /* FP32 arctangent: 0 or 2 = own minimax (one kernel, the same
                                      values), 1 = HIP atan2f */
   LK_OPT_SEGS_PER_LANE = 8,       /* FP32 kernel: segments of loop B per lane, 1/2/4, and 8 for

@@ -1427,11 +1427,14 @@ hipError_t launch_t(const DsArgs& a, int grid, hipStream_t s) {
 }
 
 // Workgroups of a kernel that are resident at once, at most `waves_per_cu` waves
-// per compute unit (0: no limit).
+// per compute unit (0: no limit), on average over the units where a workgroup has
+// more of them.
 int resident(hipError_t e, int per_cu, int waves, int n_cu, int waves_per_cu) {
   if (e != hipSuccess || per_cu < 1) per_cu = 1;
-  if (waves_per_cu > 0 && waves_per_cu < per_cu * waves)
-    per_cu = waves_per_cu >= waves ? waves_per_cu / waves : 1;
+  if (waves_per_cu > 0 && waves_per_cu < per_cu * waves) {
+    const int g = (int)((int64_t)waves_per_cu * n_cu / waves);
+    return g > 0 ? g : 1;
+  }
   return per_cu * n_cu;
 }
 
