@@ -4,7 +4,8 @@
 // chunk of segments of loop A), the partial sum of the Eq. 4 segment-pair term
 // and adds it into the pair's 128-bit fixed-point accumulator.
 //
-// Layout of the work (one 64-lane wavefront = one workgroup = one item):
+// Layout of the work (one 64-lane wavefront = one workgroup = one item; calls with
+// few pairs give an item to a workgroup of several waves, ds_team below):
 //   * each lane owns one segment (k_i, k_{i+1}) of loop B in registers;
 //   * the item's vertices of loop A are staged through LDS in tiles and every
 //     lane walks them in order (a broadcast read: all lanes read the same
@@ -206,16 +207,8 @@ __device__ __forceinline__ double angle<double, 0>(double y, double x) {
   return atan2_f64(y, x);
 }
 template <>
-__device__ __forceinline__ double angle<double, 1>(double y, double x) {
-  return atan2(y, x);
-}
-template <>
 __device__ __forceinline__ float angle<float, 2>(float y, float x) {
   return atan2_minimax(y, x, __builtin_amdgcn_rcpf(fmaxf(fabsf(x), fabsf(y))));
-}
-template <>
-__device__ __forceinline__ double angle<double, 2>(double y, double x) {
-  return atan2(y, x);
 }
 
 // LDS vertex record: 16 bytes for float (one ds_read_b128), 32 for double.
@@ -411,11 +404,13 @@ __device__ __forceinline__ void tangents(const double (&X)[R], const double (&Y)
 }
 
 // The arctangent of a small t: the full range's polynomial and Horner order from
-// a lower coefficient D on.  For |t| < lim[k] (s = t^2 below 2^-23.5 and 2^-12,
-// FP64 2^-20 and 2^-12) the coefficients above D[k] change the sum before its
-// last rounding by less than 2^-36 of its last place (FP64 2^-40), so the
-// rounded value is the full range's: for every t with D = 0, where it is 1,
-// and for all of 2e8 random t otherwise (a CPU test tries a part of them).
+// a lower coefficient D on.  For |t| < lim[k] the rounded polynomial is the full
+// range's.  Where D[k] > 0 (FP32 s = t^2 below 2^-12, FP64 2^-20 and 2^-12) the
+// coefficients above D[k] change the sum before its last rounding by less than
+// 2^-36 of its last place (FP64 2^-40); no difference in 2e8 random t (a CPU test
+// tries a part of them).  FP32's D = 0 takes 1 for 1 - s/3 + ..: below the limit
+// s/3 is less than 2^-25, half the place below 1, so the full chain rounds to 1
+// (the limit could be sqrt(3) 2^-12.5 = 2.99e-4), and t times 1 is t.
 // The angle of a term is about |s_j| |s_r| / h^2 for segments at distance h,
 // so a polyline that follows its curve has small ones: of the steps of
 // 256 terms in chainmail of 64 segments a ring, 1% have one above 1/32 and
@@ -889,12 +884,6 @@ __device__ __forceinline__ double value_scale() {
   return AT == kCrossings ? 0.5 : kInvTwoPi;
 }
 
-__device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
-
 // Wave sum of the lanes' partials.  `whole`: this item is the pair's only one,
 // so its value is final and the pair is finalised at once (`fpre`: the pair's
 // flags as the plan left them, loaded when the item started so that finishing
@@ -942,8 +931,8 @@ constexpr int waves_per_simd() {
 
 // Every variant must fit in 256 registers per lane (two waves per SIMD); a
 // test checks the compiled register counts.
-// R small pairs whose loop B fits one wave's lanes share a wave (PK, in every
-// variant).
+// R small pairs whose loop B fits one wave's lanes share a wave (PK, true in every
+// variant: part of the symbol that records of measurements name).
 template <typename Tin, typename Tc, int AT, int R, bool PK = true>
 __global__ __launch_bounds__(kWave, (waves_per_simd<Tc, AT, R>())) void ds_persistent(DsArgs A) {
   extern __shared__ __align__(16) unsigned char lds_raw[];

@@ -56,7 +56,6 @@ struct DzArgs {
   int64_t n, n_u;          // pieces and unprocessed pieces of cur (host copies)
 };
 
-// *bad (device int32, set to 0 by the caller) becomes 1 if the offsets decrease.
 // host[kHostFirst], [kHostLast]: the first and last offset; [kHostBad] = 1 if they
 // decrease anywhere (host memory the device can write, clear before the launch).
 constexpr int kHostFirst = 1, kHostLast = 2, kHostBad = 3;

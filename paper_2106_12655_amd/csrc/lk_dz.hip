@@ -234,16 +234,6 @@ __device__ __forceinline__ bool overlap(const Box& a, const Box& b) {
          (b.lo[1] <= a.hi[1]) & (a.lo[2] <= b.hi[2]) & (b.lo[2] <= a.hi[2]);
 }
 
-__device__ __forceinline__ Box shfl_box(const Box& b, int src) {
-  Box r;
-#pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    r.lo[q] = __shfl(b.lo[q], src);
-    r.hi[q] = __shfl(b.hi[q], src);
-  }
-  return r;
-}
-
 // ---------------------------------------------------------------- set-up
 // One wavefront per loop: sum of |coordinate| (for xi), fewer than 3 points
 // or a non-finite coordinate (invalid loop), and the loop's piece offsets.
@@ -279,8 +269,8 @@ __global__ __launch_bounds__(kThreads) void dz_loops_k(DzArgs A) {
   }
 }
 
-// Offsets that decrease anywhere: *bad = 1 (the host rejects the call
-// before any kernel indexes with them).
+// The first and last offset, and whether they decrease anywhere, to the host (which
+// rejects such a call before any kernel indexes with them).
 __global__ __launch_bounds__(kThreads) void dz_check_offsets_k(const int64_t* off, int32_t L,
                                                                int64_t* host) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
