@@ -196,6 +196,9 @@ __device__ __forceinline__ double atan2_f64(double y, double x) {
   return copysign(a, y);
 }
 
+// AT, the arctangent: FP32 1 = HIP's, 2 = own with short forms for small angles,
+// kFullForm = own without them; FP64 0 = own with short forms.
+constexpr int kFullForm = 4;
 template <typename T, int AT>
 __device__ __forceinline__ T angle(T y, T x);
 template <>
@@ -209,6 +212,10 @@ __device__ __forceinline__ double angle<double, 0>(double y, double x) {
 template <>
 __device__ __forceinline__ float angle<float, 2>(float y, float x) {
   return atan2_minimax(y, x, __builtin_amdgcn_rcpf(fmaxf(fabsf(x), fabsf(y))));
+}
+template <>
+__device__ __forceinline__ float angle<float, kFullForm>(float y, float x) {
+  return angle<float, 2>(y, x);
 }
 
 // LDS vertex record: 16 bytes for float (one ds_read_b128), 32 for double.
@@ -486,7 +493,7 @@ __device__ __forceinline__ T sum_small(const T (&t)[R]) {
 template <typename T, int AT, int R>
 __device__ __forceinline__ T step_angles(const T (&X)[R], const T (&Y)[R], int& full) {
   using A = SmallAngle<T>;
-  if constexpr (AT == 1) {
+  if constexpr (AT == 1 || AT == kFullForm) {
     return full_angles<T, AT, R>(X, Y);
   } else {
     T t[R];
@@ -1489,9 +1496,15 @@ bool pick_team(bool in_f64, bool compute_f64, int atan_form, int segs, Variant* 
   return true;
 }
 
+// With one segment per lane an FP32 pass of few pairs is bound by the latency of its
+// steps, which the tests for small angles lengthen: 56 pairs of 100-2,048 segments
+// take 184 us with them, 176 without, 512 of 100 75 and 70 (23,441 pairs of 64
+// segments 197 and 265).
 Variant pick(bool in_f64, bool compute_f64, int atan_form, int segs, bool unpacked = false) {
   Variant u;
   if (unpacked && pick_team(in_f64, compute_f64, atan_form, segs, &u)) return u;
+  if (unpacked && !compute_f64 && segs < 2 && (atan_form == 0 || atan_form == 2))
+    return in_f64 ? variant<double, float, kFullForm, 1>() : variant<float, float, kFullForm, 1>();
   if (compute_f64 && atan_form == kCrossings) {
     constexpr int C = kCrossings;
     if (segs >= 2) return in_f64 ? variant<double, double, C, 2>() : variant<float, double, C, 2>();
