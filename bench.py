@@ -71,17 +71,17 @@ PEAK_FP64_TFLOPS = 78.6   # MI355X published FP64 vector peak
 TRAFFIC = {
     ("chainmail", "mixed"): {
         "kernel": "_ZN2lk12_GLOBAL__N_113ds_persistentIffLi2ELi4ELb1EEEvNS_6DsArgsE",
-        "isa": "528f7142d0273737",
+        "isa": "dc69f909f8c841fa",
         "config": {"segs_per_lane": 4, "tile_a": 512, "chunk_a": 4096, "atan_form": 0},
         "fetch_scale": 2.000, "write_scale": 1.000,
         # (effective small batch, waves_per_cu) -> (FETCH_SIZE, WRITE_SIZE) KiB
         # per launch.  The runtime raises a batch below segs_per_lane to it,
         # so batches 1, 2 and 4 launch the same work here.
-        "by_launch": {(4, 0): (37032.9, 3239.9), (4, 8): (36965.5, 3231.7),
-                      (4, 12): (36995.1, 3238.9), (8, 0): (27288.4, 2321.7),
-                      (8, 8): (25768.5, 2194.7), (8, 12): (26038.8, 2324.5),
-                      (16, 0): (23918.9, 1837.1), (16, 8): (22713.8, 1687.5),
-                      (16, 12): (23073.1, 1872.9)},
+        "by_launch": {(4, 0): (36983.7, 3234.6), (4, 8): (36946.5, 3232.0),
+                      (4, 12): (36956.3, 3233.8), (8, 0): (27186.7, 2335.6),
+                      (8, 8): (25744.2, 2189.1), (8, 12): (25955.4, 2327.7),
+                      (16, 0): (23902.6, 1875.3), (16, 8): (22709.4, 1682.6),
+                      (16, 12): (23059.6, 1884.9)},
         "source": "profiles/ds_persistent_chainmail_hbm_traffic.txt",
     },
 }
